@@ -191,7 +191,7 @@ struct rsf_context {
 
 namespace {
 
-// Batch header (tile table and the three workgroup prefix tables) followed by
+// Batch header (tile table and the workgroup prefix tables) followed by
 // the tiles' regions.
 struct TileLayout {
     Grid3 g;
@@ -201,23 +201,28 @@ struct TileLayout {
 };
 
 struct BatchLayout {
-    size_t descs, start_xy, start_z, start_u, table_bytes;
+    size_t descs, start_xy, start_f, start_z, start_u, table_bytes;
     std::vector<TileLayout> tiles;
-    std::vector<int> pre_xy, pre_z, pre_u;
+    std::vector<int> pre_xy, pre_f, pre_z, pre_u;
     size_t total;
 };
 
 BatchLayout plan_layout(const rsf_tile *tiles, int n, int iters, int storage,
-                        const std::vector<Split> &splits, bool k2 = false)
+                        const std::vector<Split> &splits, bool k2 = false, int halo = 0, int nw = 4)
 {
     BatchLayout L;
     size_t off = 0;
     L.descs = off; off += align_up(sizeof(TileDesc) * (size_t)n);
-    L.start_xy = off; off += align_up(sizeof(int) * (size_t)(n + 1));
+    // two tables in one piece: a batch of up to 31 tiles needs no more room
+    // than for one
+    L.start_xy = off;
+    L.start_f = off + sizeof(int) * (size_t)(n + 1);
+    off += align_up(2 * sizeof(int) * (size_t)(n + 1));
     L.start_z = off; off += align_up(sizeof(int) * (size_t)(n + 1));
     L.start_u = off; off += align_up(sizeof(int) * (size_t)(n + 1));
     L.table_bytes = off;
     L.pre_xy.assign(1, 0);
+    L.pre_f.assign(1, 0);
     L.pre_z.assign(1, 0);
     L.pre_u.assign(1, 0);
     for (int t = 0; t < n; ++t) {
@@ -228,6 +233,7 @@ BatchLayout plan_layout(const rsf_tile *tiles, int n, int iters, int storage,
         T.T = rsf::host::tile_regions(T.g, iters, storage, k2);
         off += T.T.total;
         L.pre_xy.push_back(L.pre_xy.back() + (int)rsf::xy_blocks(T.g, T.sp));
+        L.pre_f.push_back(L.pre_f.back() + (int)rsf::xyf_blocks(T.g, T.sp, halo, nw));
         L.pre_z.push_back(L.pre_z.back() + (int)rsf::z_blocks(T.g, T.sp));
         L.pre_u.push_back(L.pre_u.back() + (int)rsf::u_blocks(T.g, T.sp));
         L.tiles.push_back(T);
@@ -387,8 +393,9 @@ struct Plan {
     BatchLayout L;
     char *base;
     TileDesc *descs;             // device
-    Batch xy, z, u, tile;
-    int64_t blocks_xy, blocks_z, blocks_u;   // grid sizes
+    Batch xy, f, z, u, tile;
+    int64_t blocks_xy, blocks_f, blocks_z, blocks_u;   // grid sizes
+    rsf::host::XyfShape shape_f; // workgroups of the iteration's xy pass
     bool k2;             // K2*I and K2*I^2 for the Sec. 4.2 force with sigma2 > 0
     int R2;
     Taps taps2;
@@ -435,7 +442,7 @@ bool fusable(const rsf_context *ctx, const rsf_params &p, bool probe, int image)
 }
 
 std::vector<Split> splits_for(rsf_context *ctx, const rsf_tile *tiles, int n, int R,
-                              bool whole_z = false);
+                              bool whole_z = false, int halo = 0);
 
 // The schedule of a batch: an autotune trial's forced choice, else the
 // autotuned choice for these tile shapes, else fused when the update keeps
@@ -466,23 +473,23 @@ bool decide_fuse(const rsf_context *ctx, const rsf_params &p, bool probe, const 
 // A tile's split when nothing is tuned for it: a single volume with the
 // built-in targets is split for the resident capacity, anything else by its
 // voxel share of the context's targets.
-Split base_split(const rsf_context *ctx, const Grid3 &g, double share, int n, int R)
+Split base_split(const rsf_context *ctx, const Grid3 &g, double share, int n, int R, int halo = 0)
 {
     const rsf::Targets tg = ctx ? ctx->targets : rsf::kDefaultTargets;
     const bool own_targets = tg.xy != rsf::kDefaultTargets.xy ||
                              tg.z != rsf::kDefaultTargets.z || tg.u != rsf::kDefaultTargets.u;
-    return n == 1 && !own_targets && R > 0 ? rsf::capacity_split(g, R)
+    return n == 1 && !own_targets && R > 0 ? rsf::capacity_split(g, R, halo)
                                            : rsf::default_split(g, share, tg);
 }
 
 std::vector<Split> splits_for(rsf_context *ctx, const rsf_tile *tiles, int n, int R,
-                              bool whole_z)
+                              bool whole_z, int halo)
 {
     const std::vector<double> sh = shares_of(tiles, n);
     std::vector<Split> splits;
     for (int t = 0; t < n; ++t) {
         const Grid3 g = grid_of(tiles[t]);
-        Split s = base_split(ctx, g, sh[t], n, R);
+        Split s = base_split(ctx, g, sh[t], n, R, halo);
         if (ctx) {
             auto it = ctx->tuned.find({g.nx, g.ny, g.nz, R});
             if (it != ctx->tuned.end() && rsf::split_valid(g, it->second)) s = it->second;
@@ -510,7 +517,12 @@ rsf_status make_plan(rsf_context *ctx, Plan &P, const rsf_tile *tiles, int n, in
     P.R2 = P.k2 ? radius_of(p.sigma2) : 0;
     if (P.k2) P.taps2 = make_taps(p.sigma2, P.R2);
     const bool fuse = decide_fuse(ctx, p, probe != nullptr, tiles, n, image);
-    P.L = plan_layout(tiles, n, iters, p.storage, splits_for(ctx, tiles, n, P.R, fuse), P.k2);
+    std::vector<Grid3> grids;
+    for (int t = 0; t < n; ++t) grids.push_back(grid_of(tiles[t]));
+    const rsf::host::XyfShape f = rsf::host::xyf_shape(grids, p.force, P.R, probe != nullptr);
+    P.shape_f = f;
+    P.L = plan_layout(tiles, n, iters, p.storage, splits_for(ctx, tiles, n, P.R, fuse, f.halo), P.k2,
+                      f.halo, f.nw);
     P.base = base;
     // the table is built on the host: in the pinned staging buffer and
     // copied, or (table_by_kernel) in a kernel argument, allocating nothing
@@ -541,6 +553,7 @@ rsf_status make_plan(rsf_context *ctx, Plan &P, const rsf_tile *tiles, int n, in
         hd[t] = d;
     }
     std::memcpy(h + P.L.start_xy, P.L.pre_xy.data(), sizeof(int) * (n + 1));
+    std::memcpy(h + P.L.start_f, P.L.pre_f.data(), sizeof(int) * (n + 1));
     std::memcpy(h + P.L.start_z, P.L.pre_z.data(), sizeof(int) * (n + 1));
     std::memcpy(h + P.L.start_u, P.L.pre_u.data(), sizeof(int) * (n + 1));
     if (table_by_kernel) {
@@ -556,6 +569,7 @@ rsf_status make_plan(rsf_context *ctx, Plan &P, const rsf_tile *tiles, int n, in
         return Batch{P.descs, reinterpret_cast<const int *>(base + start), n, {}};
     };
     P.xy = view(P.L.start_xy);
+    P.f = view(P.L.start_f);
     P.z = view(P.L.start_z);
     P.u = view(P.L.start_u);
     P.tile = Batch{P.descs, nullptr, n, {}};
@@ -566,6 +580,8 @@ rsf_status make_plan(rsf_context *ctx, Plan &P, const rsf_tile *tiles, int n, in
         sps.push_back(T.sp);
     }
     P.blocks_xy = rsf::host::balance_xcds(P.xy, rsf::host::PASS_XY, gs, sps, P.R);
+    P.blocks_f = rsf::host::balance_xcds(P.f, rsf::host::PASS_F, gs, sps, P.R, f.halo,
+                                         f.nw);
     P.blocks_z = rsf::host::balance_xcds(P.z, rsf::host::PASS_Z, gs, sps, P.R);
     P.blocks_u = rsf::host::balance_xcds(P.u, rsf::host::PASS_U, gs, sps, P.R);
     P.fuse = fuse;
@@ -583,16 +599,16 @@ rsf_status prologue(rsf_context *ctx, const Plan &P, hipStream_t s)
                     Coeffs sq = P.c;
                     for (int k = 0; k < 2 && e == hipSuccess; ++k) {
                         sq.square = k;
-                        e = rsf::launch_xy(P.R2, rsf::XY_ONE, P.image, P.storage, P.xy,
-                                           P.blocks_xy, P.taps2, sq, false, s);
+                        e = rsf::launch_xy_one(P.R2, P.image, P.storage, P.xy, P.blocks_xy, P.taps2,
+                                               sq, s);
                         if (e == hipSuccess)
                             e = rsf::launch_z_plain(P.R2, P.storage, P.z, P.blocks_z, P.taps2,
                                                     k ? rsf::Z_TO_K2I2 : rsf::Z_TO_K2I, s);
                     }
                 }
                 if (e == hipSuccess)
-                    e = rsf::launch_xy(P.R, rsf::XY_ONE, P.image, P.storage, P.xy, P.blocks_xy,
-                                       P.taps, P.c, false, s);
+                    e = rsf::launch_xy_one(P.R, P.image, P.storage, P.xy, P.blocks_xy, P.taps, P.c,
+                                           s);
                 if (e == hipSuccess)
                     e = rsf::launch_z_plain(P.R, P.storage, P.z, P.blocks_z, P.taps, rsf::Z_TO_KI,
                                             s);
@@ -626,20 +642,13 @@ rsf_status iteration(rsf_context *ctx, const Plan &P, bool probe, hipStream_t s,
     }
     const bool paper = P.c.force == RSF_FORCE_PAPER;
     HIP_TRY(timed(ctx, RSF_PASS_XY_FITS, s, [&] {
-                return rsf::launch_xy(P.R,
-                                      paper ? (P.k2 ? rsf::XY_PAPER2 : rsf::XY_PAPER)
-                                            : rsf::XY_FITS,
-                                      P.image,
-                                      P.storage, P.xy, P.blocks_xy, P.taps, P.c, probe, s);
+                return rsf::launch_xyf(P.R,
+                                       paper ? (P.k2 ? rsf::XY_PAPER2 : rsf::XY_PAPER)
+                                             : rsf::XY_RSF,
+                                       P.image, P.storage, P.f, P.blocks_f, P.shape_f.nw,
+                                       P.shape_f.threads, P.taps, P.c, probe, s);
             }),
-            "xy(fits)");
-    // the Sec. 4.2 force with sigma2 = 0 needs no second Gaussian stage
-    if (!paper)
-        HIP_TRY(timed(ctx, RSF_PASS_XY_FORCE, s, [&] {
-                    return rsf::launch_xy(P.R, rsf::XY_TWO, P.image, P.storage, P.xy,
-                                          P.blocks_xy, P.taps, P.c, probe, s);
-                }),
-                "xy(g)");
+            "xy");
     HIP_TRY(timed(ctx, RSF_PASS_Z_UPDATE, s, [&] {
                 if (fused)
                     return rsf::launch_z_update_fused(P.R, P.image, P.storage, u, P.blocks_u,
@@ -711,9 +720,10 @@ rsf_status run_iterations(rsf_context *ctx, const Plan &P, int iters, hipStream_
         append_key(key, &P.storage, sizeof(P.storage));
         append_key(key, &P.taps, sizeof(P.taps));
         append_key(key, &P.c, sizeof(P.c));
-        for (const Batch *b : {&P.xy, &P.z, &P.u, &P.tile}) append_key(key, b, sizeof(Batch));
-        for (const int64_t *v : {&P.blocks_xy, &P.blocks_z, &P.blocks_u})
+        for (const Batch *b : {&P.xy, &P.f, &P.z, &P.u, &P.tile}) append_key(key, b, sizeof(Batch));
+        for (const int64_t *v : {&P.blocks_xy, &P.blocks_f, &P.blocks_z, &P.blocks_u})
             append_key(key, v, sizeof(*v));
+        append_key(key, &P.shape_f, sizeof(P.shape_f));
         append_key(key, &P.k2, sizeof(P.k2));
         if (!ctx->graph_exec || key != ctx->graph_key) {
             rsf_status st = retire_graph(ctx);

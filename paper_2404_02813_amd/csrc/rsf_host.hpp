@@ -180,7 +180,27 @@ inline TileDesc tile_desc(const Grid3 &g, const Split &sp, const void *volume, f
 // inside the tile (those outside are zero padding and never loaded).
 // ---------------------------------------------------------------------------
 
-enum PassKind { PASS_XY, PASS_Z, PASS_U };
+enum PassKind { PASS_XY, PASS_Z, PASS_U, PASS_F };
+
+// Columns neighbouring strips of the xy pass share: R with two Gaussian
+// stages in the pass (RSF force), none with one.
+inline int xyf_halo(int force, int R) { return force == RSF_FORCE_PAPER ? 0 : R; }
+
+// The xy pass's workgroups for a batch: most waves of one (probes run with
+// 4), and the threads its widest strip needs.
+struct XyfShape {
+    int halo, nw, threads;
+};
+inline XyfShape xyf_shape(const std::vector<Grid3> &g, int force, int R, bool probe)
+{
+    XyfShape f{xyf_halo(force, R), 4, 64};
+    int least = 0;
+    for (const Grid3 &q : g) least = least == 0 ? q.nx : std::min(least, q.nx);
+    if (!probe && g.size() == 1) f.nw = xyf_pick(g[0], R, f.halo).nw;
+    else if (!probe && !g.empty()) f.nw = xyf_waves(least, f.halo);
+    for (const Grid3 &q : g) f.threads = std::max(f.threads, xyf_threads(q.nx, f.halo, f.nw));
+    return f;
+}
 
 inline int64_t span_cost(int n, int chunks, int idx, int R)
 {
@@ -189,8 +209,10 @@ inline int64_t span_cost(int n, int chunks, int idx, int R)
     return (int64_t)(b - a) + std::min(R, a) + std::min(R, n - b);
 }
 
-inline int64_t blocks_of(PassKind k, const Grid3 &g, const Split &s)
+// `halo`, `nw`: the xy pass's strips (PASS_F).
+inline int64_t blocks_of(PassKind k, const Grid3 &g, const Split &s, int halo = 0, int nw = 4)
 {
+    if (k == PASS_F) return xyf_blocks(g, s, halo, nw);
     return k == PASS_XY ? xy_blocks(g, s) : (k == PASS_Z ? z_blocks(g, s) : u_blocks(g, s));
 }
 
@@ -198,17 +220,22 @@ inline int64_t blocks_of(PassKind k, const Grid3 &g, const Split &s)
 // order) into kXcds contiguous ranges of about equal total cost, write them
 // to b.xcd and return the grid size (kXcds times the longest range).
 inline int64_t balance_xcds(Batch &b, PassKind k, const std::vector<Grid3> &g,
-                            const std::vector<Split> &sp, int R)
+                            const std::vector<Split> &sp, int R, int halo = 0, int nw = 4)
 {
+    const bool rows = k == PASS_XY || k == PASS_F;
+    const auto chunks_in = [&](size_t t) {
+        return k == PASS_XY ? sp[t].xy : (k == PASS_Z ? sp[t].z : (k == PASS_U ? sp[t].u : sp[t].f));
+    };
+    const int reach = k == PASS_F ? R + halo : R;
     // per-tile: workgroups and the cost of each of its (repeating) chunks
     double total = 0.0;
     int64_t nblocks = 0;
     for (size_t t = 0; t < g.size(); ++t) {
-        const int nch = k == PASS_XY ? sp[t].xy : (k == PASS_Z ? sp[t].z : sp[t].u);
-        const int n = k == PASS_XY ? g[t].ny : g[t].nz;
+        const int nch = chunks_in(t);
+        const int n = rows ? g[t].ny : g[t].nz;
         double per = 0.0;   // cost of one full cycle of chunks
-        for (int c = 0; c < nch; ++c) per += (double)span_cost(n, nch, c, R);
-        const int64_t nb = blocks_of(k, g[t], sp[t]);
+        for (int c = 0; c < nch; ++c) per += (double)span_cost(n, nch, c, reach);
+        const int64_t nb = blocks_of(k, g[t], sp[t], halo, nw);
         total += per * (double)(nb / nch);
         nblocks += nb;
     }
@@ -218,14 +245,14 @@ inline int64_t balance_xcds(Batch &b, PassKind k, const std::vector<Grid3> &g,
     int64_t gb = 0;
     b.xcd[0] = 0;
     for (size_t t = 0; t < g.size() && cut < kXcds; ++t) {
-        const int64_t nb = blocks_of(k, g[t], sp[t]);
-        const int nch = k == PASS_XY ? sp[t].xy : (k == PASS_Z ? sp[t].z : sp[t].u);
-        const int n = k == PASS_XY ? g[t].ny : g[t].nz;
-        const int nbx = nbx64(g[t].nx);
+        const int64_t nb = blocks_of(k, g[t], sp[t], halo, nw);
+        const int nch = chunks_in(t);
+        const int n = rows ? g[t].ny : g[t].nz;
+        const int nbx = k == PASS_F ? xyf_strips(g[t].nx, halo, nw).n : nbx64(g[t].nx);
         for (int64_t lb = 0; lb < nb && cut < kXcds; ++lb, ++gb) {
             // chunk index of workgroup lb in the tile's workgroup order
-            const int c = k == PASS_XY ? (int)((lb / nbx) % nch) : (int)(lb % nch);
-            const double w = (double)span_cost(n, nch, c, R);
+            const int c = rows ? (int)((lb / nbx) % nch) : (int)(lb % nch);
+            const double w = (double)span_cost(n, nch, c, reach);
             // the cut goes before this workgroup if that is nearer the target
             while (cut < kXcds && acc + 0.5 * w >= total * cut / kXcds) b.xcd[cut++] = (int)gb;
             acc += w;

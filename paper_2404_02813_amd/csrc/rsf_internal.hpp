@@ -17,6 +17,7 @@ namespace rsf {
 
 constexpr int kMaxR = 16;          // largest Gaussian radius (sigma <= 16/3)
 constexpr int kXcds = 8;           // accelerator complex dies, each with its own L2
+constexpr int kCus = 256;           // compute units
 constexpr int kThreads = 256;      // z pass block: consecutive columns
 constexpr int kUx = 64;            // update pass: columns per block along x
 constexpr int kUy = 8;             // update pass: columns per block along y
@@ -44,6 +45,7 @@ struct Grid3 {
 // z chunks of the stage-1 z pass and of the update pass.
 struct Split {
     int xy, z, u;
+    int f = 1;   // row chunks of the iteration's xy pass
 };
 
 // One tile of a batch as the kernels see it (device pointers).
@@ -72,7 +74,7 @@ struct Coeffs {
     float eta;
     int reg;                        // 0 double well, 1 single well
     int force;                      // 0 RSF e_i (sigma), 1 Sec. 4.2 form (sigma2)
-    int square;                     // XY_ONE: convolve I^2 instead of I
+    int square;                     // xy pass of K*I: convolve I^2 instead of I
     double tol;                     // stop a tile once sum|dphi| / voxels < tol (0: never)
 };
 
@@ -110,6 +112,56 @@ __host__ __device__ inline int64_t u_blocks(const Grid3 &g, const Split &s)
     return (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy) * s.u;
 }
 
+// Strips of the iteration's xy pass: a workgroup of up to `nw` waves (64
+// columns each) computes the `width` columns from xyf_first and stores all
+// but the `halo` columns it shares with a neighbouring strip.  Of the few
+// smallest strip counts, the one with the fewest waves in all.  With more
+// than one strip every strip is at least 128 wide, so that its threads can
+// load a group's x halo (8 R elements) at one each; the last one is moved
+// left to its full width.
+struct XyfStrips {
+    int n, width, step;
+};
+__host__ __device__ inline XyfStrips xyf_strips(int nx, int halo, int nw)
+{
+    const int most = 64 * nw;
+    if (nx <= most) return XyfStrips{1, nx, nx};
+    const int full = most - 2 * halo;
+    const int least = (nx - 2 * halo + full - 1) / full;
+    XyfStrips best{0, 0, 0};
+    int waves = 0;
+    for (int n = least; n < least + 4; ++n) {
+        const int w = (int)(((int64_t)nx + (int64_t)2 * halo * (n - 1) + n - 1) / n);
+        if (n > least && w < 128) break;
+        const int step = w - 2 * halo;
+        const int m = (nx - 2 * halo + step - 1) / step;   // strips that hold a column of their own
+        const int k = m * ((w + 63) / 64);
+        if (best.n == 0 || k < waves) {
+            best = XyfStrips{m, w, step};
+            waves = k;
+        }
+    }
+    return best;
+}
+// Threads of the workgroup that covers a strip.
+__host__ __device__ inline int xyf_threads(int nx, int halo, int nw)
+{
+    return (xyf_strips(nx, halo, nw).width + 63) / 64 * 64;
+}
+// Most waves of a workgroup (4 or 8) for a batch of several tiles whose
+// narrowest has `nx` columns (a single volume: xyf_pick).  Two stages in the pass recompute a 2R-column halo per strip,
+// so rows longer than 256 go to workgroups of 8 waves (512^3, R = 9: one
+// 512-column strip 0.62 ms, three of 183 columns 0.74 ms); narrower tiles
+// would leave half of such a workgroup's LDS unused (a batch of 114- to
+// 274-column tiles: 0.74 ms with 4, 1.33 ms with 8).  One stage has no halo
+// to recompute.
+__host__ __device__ inline int xyf_waves(int nx, int halo) { return halo > 0 && nx > 256 ? 8 : 4; }
+// Workgroups of a tile in the iteration's xy pass.
+__host__ __device__ inline int64_t xyf_blocks(const Grid3 &g, const Split &s, int halo, int nw)
+{
+    return (int64_t)xyf_strips(g.nx, halo, nw).n * s.f * g.nz;
+}
+
 // Workgroups a whole batch aims at per pass: xy waves, z-pass workgroups,
 // update-pass workgroups.
 struct Targets {
@@ -126,11 +178,32 @@ Split default_split(const Grid3 &g, double share = 1.0, const Targets &tg = kDef
 // Split of a single volume from the resident capacity of the z and update
 // passes (R: Gaussian radius): z chunks are chosen so that the launches' last
 // round of workgroups is not left nearly empty.
-Split capacity_split(const Grid3 &g, int R);
+Split capacity_split(const Grid3 &g, int R, int halo);
 // Workgroups the GPU keeps resident at once: z passes (256-thread groups at
 // 8 per CU) and the update pass (512-thread groups at 2 per CU), on 256 CUs.
 constexpr int64_t kResidentZ = 2048;
 constexpr int64_t kResidentU = 512;
+// Workgroups of `waves` waves of the xy pass resident at once: 3 waves per
+// SIMD up to radius 9, 2 above (registers); at most 4 groups per CU, 2 of
+// the large ones (LDS).
+inline int64_t resident_f(int R, int nw, int waves)
+{
+    const int by_regs = (R <= 9 ? 12 : 8) / waves, by_lds = nw == 8 ? 2 : 4;
+    const int per_cu = by_regs < by_lds ? by_regs : by_lds;
+    return kCus * (int64_t)(per_cu < 1 ? 1 : per_cu);
+}
+// Workgroup size (4 or 8 waves) and row chunks of the xy pass for a single
+// volume: the least time of the busiest CU, in rows.  A step of four rows
+// takes a SIMD about 2600 clocks per resident wave (it is bound by the matrix
+// and vector units) and no less than about 3900 (one wave's own latency), so
+// the time is rounds of resident workgroups x rows (the chunk, `halo` rows of
+// its own and its neighbours' on either side, two groups of latency) x
+// max(1.5, waves per SIMD).  192 x 320 x 352, R = 9, FP16 fields: two strips
+// of 3 waves in two chunks 0.76 x the time of one strip of 6 waves.
+struct XyfPick {
+    int nw, f;
+};
+XyfPick xyf_pick(const Grid3 &g, int R, int halo);
 // Update-pass workgroups of a tile under any valid split are at most this.
 __host__ __device__ inline int64_t u_blocks_max(const Grid3 &g)
 {
@@ -140,12 +213,12 @@ bool split_valid(const Grid3 &g, const Split &s);
 
 bool types_supported(int R, int image_dtype, int storage_dtype);
 
-// xy pass modes: XY_ONE reads the image (or its square) and writes one field
-// (P), for K*I; XY_FITS reads the pair P and K*I and writes the pair Q;
-// XY_TWO reads the pair Q and writes the pair P; XY_PAPER reads the pair P,
-// K*I and the image and writes the Sec. 4.2 force with sigma2 = 0 to Q as
-// float; XY_PAPER2 reads K2*I and K2*I^2 in place of the image (sigma2 > 0).
-enum XyMode { XY_ONE = 0, XY_TWO = 1, XY_FITS = 2, XY_PAPER = 3, XY_PAPER2 = 4 };
+// Modes of the iteration's xy pass: XY_RSF reads the pair P and K*I and writes
+// the pair Q = Kxy*(g1, g2); XY_PAPER reads the pair P, K*I and the image and
+// writes the Sec. 4.2 force with sigma2 = 0 to Q as float; XY_PAPER2 reads
+// K2*I and K2*I^2 in place of the image (sigma2 > 0).  (The numbers follow
+// those the profiles name.)
+enum XyMode { XY_PAPER = 3, XY_PAPER2 = 4, XY_RSF = 5 };
 // Where the plain z pass writes: K*I, K2*I or K2*I^2.
 enum ZTarget { Z_TO_KI = 0, Z_TO_K2I = 1, Z_TO_K2I2 = 2 };
 
@@ -159,8 +232,15 @@ struct TableBlob {
     uint32_t w[kTableBlobBytes / 4];
 };
 hipError_t launch_put_table(void *dst, const TableBlob &blob, int bytes, hipStream_t s);
-hipError_t launch_xy(int R, int mode, int image_dtype, int storage_dtype, const Batch &b,
-                     int64_t blocks, const Taps &t, const Coeffs &c, bool probe, hipStream_t s);
+// The image (or its square) -> the field P, for K*I.
+hipError_t launch_xy_one(int R, int image_dtype, int storage_dtype, const Batch &b, int64_t blocks,
+                         const Taps &t, const Coeffs &c, hipStream_t s);
+// The iteration's xy pass: P (and K*I, ...) -> Q (mode XY_RSF, XY_PAPER, XY_PAPER2).
+// `nw`: 4 or 8 (xyf_waves); `threads`: 64 times the most waves a strip of
+// the batch's tiles holds.
+hipError_t launch_xyf(int R, int mode, int image_dtype, int storage_dtype, const Batch &b,
+                      int64_t blocks, int nw, int threads, const Taps &t, const Coeffs &c, bool probe,
+                      hipStream_t s);
 // K*I: the z pass of P into KI.
 hipError_t launch_z_plain(int R, int storage_dtype, const Batch &b, int64_t blocks,
                           const Taps &t, int target, hipStream_t s);
@@ -168,7 +248,7 @@ hipError_t launch_z_plain(int R, int storage_dtype, const Batch &b, int64_t bloc
 hipError_t launch_z_heaviside(int R, int image_dtype, int storage_dtype, const Batch &b,
                               int64_t blocks, const Taps &t, const Coeffs &c, bool probe,
                               hipStream_t s);
-// Stage-2 z pass of the pair P = (Kxy*g1, Kxy*g2) and the update into the
+// Stage-2 z pass of the pair Q = (Kxy*g1, Kxy*g2) and the update into the
 // other phi buffer, with per-block |dphi| partial sums.
 hipError_t launch_z_update(int R, int image_dtype, int storage_dtype, const Batch &b,
                            int64_t blocks, const Taps &t, const Coeffs &c, bool probe,
@@ -251,8 +331,11 @@ hipError_t launch_offset(const float *u, float *phi, int64_t n, float offset, hi
 
 // Per-radius, per-type launchers behind the dispatchers (rsf_kernels.hpp).
 template <int R, class IT, class ST>
-hipError_t launch_xy_r(int mode, const Batch &b, int64_t blocks, const Taps &t, const Coeffs &c,
-                       bool probe, hipStream_t s);
+hipError_t launch_xy_one_r(const Batch &b, int64_t blocks, const Taps &t, const Coeffs &c,
+                           hipStream_t s);
+template <int R, class IT, class ST>
+hipError_t launch_xyf_r(int mode, const Batch &b, int64_t blocks, int nw, int threads, const Taps &t,
+                        const Coeffs &c, bool probe, hipStream_t s);
 template <int R, class ST>
 hipError_t launch_z_plain_r(const Batch &b, int64_t blocks, const Taps &t, int target,
                             hipStream_t s);

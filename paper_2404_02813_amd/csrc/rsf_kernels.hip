@@ -1,24 +1,23 @@
 // HIP kernels (gfx950) of one RSF level-set iteration.
 //
-// One iteration = four bandwidth-bound passes plus a tiny reduction:
+// One iteration = three passes plus a tiny reduction:
 //   z(H)     : (phi, I) -> Kz*(H I), Kz*H           H = H_eps(phi)      (Sec. 3)
-//   xy(fits) : -> A1 = K*(H I), B1 = K*H, with A2 = K*I - A1, B2 = K*1 - B1
+//   xy       : -> A1 = K*(H I), B1 = K*H, with A2 = K*I - A1, B2 = K*1 - B1
 //              f1 = A1/B1, f2 = A2/B2, g1 = l1 f1 - l2 f2,
 //              g2 = l1 f1^2 - l2 f2^2                                    (Sec. 3)
-//   xy(two)  : (g1, g2) -> Kxy*g1, Kxy*g2
+//              -> Kxy*g1, Kxy*g2
 //   z(upd)   : Fd = (l1-l2) I^2 K*1 - 2 I K*g1 + K*g2 = l1 e1 - l2 e2,
 //              curvature, regulariser, Dirac-weighted explicit update   (Sec. 2-3)
 //              and per-block FP64 partial sums of |phi' - phi|
 //   reduce   : fixed-order FP64 sum of the partials.
 // The separable Gaussian is applied as z passes (each thread marches one
-// (x, y) column through a z chunk with a register ring of 2R+1 slices) and xy
-// passes (a wave marches a 64-wide strip down a row chunk: rows staged in LDS
-// and x-convolved, a register ring of 2R+1 rows for y), so every global
-// access is coalesced along x.  Stage 1 runs z first, so H_eps is evaluated
-// once per voxel; stage 2 runs z last, so the update sees the z window it
-// needs.  Every pass is one launch over a batch of tiles; workgroups are
-// numbered so that each of the 8 XCDs works on one contiguous range, keeping
-// halo re-reads within one L2.
+// (x, y) column through a z chunk with a register ring of 2R+1 slices) and an
+// xy pass (a workgroup marches down the rows of a slice, convolving each of
+// them on the matrix cores), so every global access is coalesced along x.
+// Stage 1 runs z first, so H_eps is evaluated once per voxel; stage 2 runs z
+// last, so the update sees the z window it needs.  Every pass is one launch
+// over a batch of tiles; workgroups are numbered so that each of the 8 XCDs
+// works on one contiguous range, keeping halo re-reads within one L2.
 #include <algorithm>
 #include <cmath>
 
@@ -582,11 +581,20 @@ bool types_supported(int R, int it, int st)
     }                                                                                   \
     return hipErrorInvalidValue;
 
-hipError_t launch_xy(int R, int mode, int it, int st, const Batch &b, int64_t blocks,
-                     const Taps &t, const Coeffs &c, bool probe, hipStream_t s)
+hipError_t launch_xy_one(int R, int it, int st, const Batch &b, int64_t blocks, const Taps &t,
+                         const Coeffs &c, hipStream_t s)
 {
 #define C(RR, IT, ST) \
-    case RR: return launch_xy_r<RR, IT, ST>(mode, b, blocks, t, c, probe, s);
+    case RR: return launch_xy_one_r<RR, IT, ST>(b, blocks, t, c, s);
+    RSF_DISPATCH(C)
+#undef C
+}
+
+hipError_t launch_xyf(int R, int mode, int it, int st, const Batch &b, int64_t blocks,
+                      int nw, int threads, const Taps &t, const Coeffs &c, bool probe, hipStream_t s)
+{
+#define C(RR, IT, ST) \
+    case RR: return launch_xyf_r<RR, IT, ST>(mode, b, blocks, nw, threads, t, c, probe, s);
     RSF_DISPATCH(C)
 #undef C
 }

@@ -6,56 +6,34 @@
 #include <type_traits>
 
 #include "rsf_device.hpp"
+#include "rsf_xyf.hpp"
 
 namespace rsf {
 
 namespace {
 
 // ---------------------------------------------------------------------------
-// xy pass as a march along y.  One wave owns a 64-wide strip of one z slice
-// and a chunk of rows.  Each incoming row (with an R halo in x) is staged in
-// LDS, convolved along x (one output per lane), and pushed into a per-lane
-// register ring of 2R+1 rows, from which the y convolution is taken; x halo
-// work is paid only on the chunk's 2R extra rows, never per row.
+// xy pass of one field, for K*I (and K2*I, K2*I^2), once per evolution: a
+// march along y.  One wave owns a 64-wide strip of one z slice and a chunk of
+// rows.  Each incoming row (with an R halo in x) is staged in LDS, convolved
+// along x (one output per lane), and pushed into a per-lane register ring of
+// rows, from which the y convolution is taken; x halo work is paid only on
+// the chunk's 2R extra rows, never per row.
 // ---------------------------------------------------------------------------
 
-// XY_ONE reads the image (IN) and writes one field P (ST), for K*I; XY_FITS
-// reads the pair P and K*I and writes the pair Q; XY_TWO reads the pair Q and
-// writes the pair P; XY_PAPER reads the pair P, K*I and the image (IMG) and
-// writes the force of Sec. 4.2 with sigma2 = 0 to Q as float.
 // At least five waves per SIMD (at most 96 registers) where the ring of
-// 2R + 2 rows and the stages fit without spilling: radius <= 8, or 9 except
-// for the fits of 16-bit storage.  Otherwise, and for the Sec. 4.2 force
-// modes (more pointwise inputs), the compiler's own choice (no bound).
-template <int R, int MODE, class ST>
-constexpr int xy_waves_per_eu =
-    (MODE == XY_ONE || MODE == XY_TWO || MODE == XY_FITS) &&
-            (R <= 8 || (R == 9 && (std::is_same<ST, float>::value || MODE != XY_FITS)))
-        ? 5
-        : 1;
-
-template <int R, int MODE, class IN, class ST, class IMG = float>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(xy_waves_per_eu<R, MODE, ST>)))
-void xy_kernel(Batch bt, Taps t, Coeffs c)
+// 2R + 2 rows and the stages fit without spilling; otherwise the compiler's
+// own choice (no bound).
+template <int R, class IN, class ST>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(R <= 9 ? 5 : 1)))
+void xy_one_kernel(Batch bt, Taps t, Coeffs c)
 {
-    constexpr bool PAPER_F = MODE == XY_PAPER || MODE == XY_PAPER2;
-    constexpr bool FITS = MODE == XY_FITS || PAPER_F;
-    constexpr int NF = MODE == XY_ONE ? 1 : 2;
     constexpr int W = 2 * R + 1;
     constexpr int RW = 64 + 2 * R;
     static_assert(RW <= 128, "a staged row is two loads per lane");
     // rows are written whole (128 entries, the tail past RW is never read)
     // so that staging has no branch
-    __shared__ float row[2][NF][128];
-    // FP16 pairs are staged as they are loaded, both fields in one word, and
-    // converted by the x convolution's mixed-precision FMAs (exactly, as a
-    // conversion at staging would): half the LDS traffic, no conversions
-    constexpr bool PACKROW = NF == 2 && std::is_same<IN, _Float16>::value;
-    // Other pairs are staged interleaved, (a, b) per column, so one 64-bit
-    // LDS read serves a tap of both fields (and a 128-bit pair read two
-    // taps): half the LDS instructions of two separate rows, the same bytes.
-    constexpr bool PAIRROW = NF == 2 && !PACKROW;
-    __shared__ float2 rowp[2][PAIRROW ? 128 : 1];
+    __shared__ float row[2][128];
 
     Where wh;
     if (!locate(bt, wh)) return;
@@ -63,8 +41,6 @@ void xy_kernel(Batch bt, Taps t, Coeffs c)
     if (glb(d.flags)[0]) return;
     const Grid3 g = d.g;
     const int nyc = d.sp.xy;
-    const void *__restrict__ in_ = MODE == XY_ONE ? d.I : (FITS ? d.P : d.Q);
-    void *__restrict__ out_ = FITS ? d.Q : d.P;
     const int nbx = (g.nx + 63) / 64;
     const int tile = wh.lb;
     const int xs = tile % nbx, rest = tile / nbx;
@@ -81,13 +57,11 @@ void xy_kernel(Batch bt, Taps t, Coeffs c)
     // sits under a branch, so waiting for one row leaves later rows in
     // flight.
     struct Raw {
-        Vec2<IN> p[2];
         IN s[2];
     };
     // the slice through a buffer descriptor: a row is a uniform byte offset,
     // each lane's column a loop-invariant 32-bit one
-    const rsrc_t rin = rsrc(static_cast<const char *>(in_) +
-                            zb * (int64_t)(NF == 2 ? sizeof(Pair<IN>) : sizeof(IN)));
+    const rsrc_t rin = rsrc(static_cast<const IN *>(d.I) + zb);
     uint32_t gxo[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -99,114 +73,56 @@ void xy_kernel(Batch bt, Taps t, Coeffs c)
         Raw r;
         const int yy = min(max(y, 0), g.ny - 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (NF == 2)
-                r.p[h] = bld<Vec2<IN>>(rin, gxo[h], (uint32_t)(yy * g.nx) * (uint32_t)sizeof(Pair<IN>));
-            else
-                r.s[h] = bld<IN>(rin, gxo[h], (uint32_t)(yy * g.nx) * (uint32_t)sizeof(IN));
-        }
+        for (int h = 0; h < 2; ++h)
+            r.s[h] = bld<IN>(rin, gxo[h], (uint32_t)(yy * g.nx) * (uint32_t)sizeof(IN));
         return r;
     };
     // Stage row y (fetched) into LDS slot `slot`, run `between` (work that
-    // does not touch the row: the next y convolution, whose two sums it
-    // returns), x-convolve the row and return the lane's value.  `between`
-    // and the x-convolution's LDS reads share one scheduling region (the
-    // wave sync opens it, one `pin` of all four sums closes it), so its FMAs
-    // can fill the reads' latency.  Values outside the slice are zeroed by a
-    // bit mask, not a branch, so staging opens no new region either.
-    auto xrow = [&](const Raw &r, int y, int slot, auto &&between, float2 &yv) -> float2 {
+    // does not touch the row: the next y convolution, whose sum it returns),
+    // x-convolve the row and return the lane's value.  `between` and the
+    // x-convolution's LDS reads share one scheduling region (the wave sync
+    // opens it, one `pin` of both sums closes it), so its FMAs can fill the
+    // reads' latency.  Values outside the slice are zeroed by a bit mask, not
+    // a branch, so staging opens no new region either.
+    auto xrow = [&](const Raw &r, int y, int slot, auto &&between, float &yv) -> float {
         const bool yok = y >= 0 && y < g.ny;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int j = lane + 64 * h;
             const int gx = x0 - R + j;
             const int keep = (yok && gx >= 0 && gx < g.nx) ? -1 : 0;
-            auto masked = [&](float v) { return __int_as_float(__float_as_int(v) & keep); };
-            if constexpr (PACKROW) {
-                const uint32_t bits = __builtin_bit_cast(uint32_t, r.p[h]) & (uint32_t)keep;
-                row[slot][0][j] = __builtin_bit_cast(float, bits);
-            } else if constexpr (PAIRROW) {
-                rowp[slot][j] = make_float2(masked(to_f(r.p[h].x)), masked(to_f(r.p[h].y)));
-            } else if (NF == 2) {
-                row[slot][0][j] = masked(to_f(r.p[h].x));
-                row[slot][NF - 1][j] = masked(to_f(r.p[h].y));
-            } else {
-                const float v = masked(to_f(r.s[h]));
-                row[slot][0][j] = c.square ? v * v : v;
-            }
+            const float v = __int_as_float(__float_as_int(to_f(r.s[h])) & keep);
+            row[slot][j] = c.square ? v * v : v;
         }
         // the workgroup is one wave: order its LDS writes before the reads
         // (a workgroup barrier's fence would also wait for the global stores
         // and loads in flight)
         __syncwarp();
         yv = between();
-        float ca = 0.f, cb = 0.f;
+        float ca = 0.f;
 #pragma unroll
-        for (int k = 0; k < W; ++k) {
-            if constexpr (PACKROW) {
-                const Vec2<_Float16> v = __builtin_bit_cast(Vec2<_Float16>, row[slot][0][lane + k]);
-                ca = fmaf(tap<R>(t, k), (float)v.x, ca);
-                cb = fmaf(tap<R>(t, k), (float)v.y, cb);
-            } else if constexpr (PAIRROW) {
-                const float2 v = rowp[slot][lane + k];
-                ca = fmaf(tap<R>(t, k), v.x, ca);
-                cb = fmaf(tap<R>(t, k), v.y, cb);
-            } else {
-                ca = fmaf(tap<R>(t, k), row[slot][0][lane + k], ca);
-                if (NF == 2) cb = fmaf(tap<R>(t, k), row[slot][NF - 1][lane + k], cb);
-            }
-        }
-        __asm__ volatile("" : "+v"(ca), "+v"(cb), "+v"(yv.x), "+v"(yv.y));
-        return make_float2(ca, cb);
+        for (int k = 0; k < W; ++k) ca = fmaf(tap<R>(t, k), row[slot][lane + k], ca);
+        __asm__ volatile("" : "+v"(ca), "+v"(yv));
+        return ca;
     };
-    auto nothing = [] { return make_float2(0.f, 0.f); };
+    auto nothing = [] { return 0.f; };
 
-    // Prefetch depth as in the update pass: two stages (a row and the
-    // pointwise inputs of one step) alternate by step parity where the
-    // registers allow.  The x convolution runs one row ahead of the y
-    // convolution: step y x-convolves row y + R + 1 (for the next step) while
-    // it y-convolves output y from rows already in the ring, so the LDS reads
-    // of the one overlap the FMAs of the other.  The ring therefore holds
-    // 2R + 2 rows, and the march is unrolled by M = 2R + 2 (even, as the
-    // alternating stages need).
+    // Two stages of loads in flight (one above radius 10, whose rings take
+    // the registers) alternate by step parity.  The x convolution runs one
+    // row ahead of the y convolution: step y x-convolves row y + R + 1 (for
+    // the next step) while it y-convolves output y from rows already in the
+    // ring, so the LDS reads of the one overlap the FMAs of the other.  The
+    // ring therefore holds 2R + 2 rows, and the march is unrolled by
+    // M = 2R + 2 (even, as the alternating stages need).
     constexpr int PF = R <= 10 ? 2 : 1;
     constexpr int M = W + 1;
     const int xc = min(x, g.nx - 1);
     const int last = min(63, g.nx - 1 - x0);   // last in-slice lane of the strip
-    const rsrc_t rki = rsrc(static_cast<const ST *>(d.KI) + zb);
-    const rsrc_t rim = rsrc(static_cast<const IMG *>(d.I) + zb);
-    const rsrc_t rk2i = rsrc(static_cast<const ST *>(d.K2I) + zb);
-    const rsrc_t rk2q = rsrc(static_cast<const ST *>(d.K2I2) + zb);
-    const float cxz = FITS ? glb(d.cx)[xc] * glb(d.cz)[z] : 0.f;
-    const float *const cyp = d.cy;   // read once: the loop's stores could alias the table
-    // the loads of step y: row y + R + 1 and the fits' pointwise inputs of row y
-    struct Stage {
-        Raw row;
-        ST ki, k2i, k2q;
-        IMG im;
-        float cy;
-    };
-    auto stage = [&](int y) {
-        Stage st;
-        st.row = fetch(y + R + 1);
-        if (FITS) {
-            const int yy = min(y, g.ny - 1);
-            const uint32_t row = (uint32_t)(yy * g.nx);
-            st.ki = bld<ST>(rki, (uint32_t)xc, row * (uint32_t)sizeof(ST));
-            st.cy = uniform_ld(cyp, yy);   // one value for the wave: a scalar load
-            if (MODE == XY_PAPER) st.im = bld<IMG>(rim, (uint32_t)xc, row * (uint32_t)sizeof(IMG));
-            if (MODE == XY_PAPER2) {
-                st.k2i = bld<ST>(rk2i, (uint32_t)xc, row * (uint32_t)sizeof(ST));
-                st.k2q = bld<ST>(rk2q, (uint32_t)xc, row * (uint32_t)sizeof(ST));
-            }
-        }
-        return st;
-    };
 
     // prologue: rows y0 - R .. y0 + R x-convolved into ring slots 0..2R (row
     // y0 - R + j staged in LDS slot j & 1)
-    float ra[M], rb[M];
-    Stage sa, sb;
+    float ra[M];
+    Raw sa, sb;
     {
         Raw nxt = fetch(y0 - R);
 #pragma unroll
@@ -215,98 +131,37 @@ void xy_kernel(Batch bt, Taps t, Coeffs c)
             if (j < 2 * R) {
                 nxt = fetch(y0 - R + j + 1);
             } else {
-                sa = stage(y0);
-                if (PF == 2) sb = stage(y0 + 1);
+                sa = fetch(y0 + R + 1);
+                if (PF == 2) sb = fetch(y0 + R + 2);
             }
-            float2 unused;
-            const float2 v = xrow(cur, y0 - R + j, j & 1, nothing, unused);
-            ra[j] = v.x;
-            rb[j] = v.y;
+            float unused;
+            ra[j] = xrow(cur, y0 - R + j, j & 1, nothing, unused);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    const gptr<float> probe_f1 = glb(d.probe_f1), probe_f2 = glb(d.probe_f2),
-                      probe_fd = glb(d.probe_Fd);
-    // outputs of the slice: one ST field, the pair, or the float force
-    const rsrc_t rout = rsrc(static_cast<char *>(out_) +
-                             zb * (int64_t)(PAPER_F ? sizeof(float)
-                                                    : (NF == 2 ? sizeof(Pair<ST>) : sizeof(ST))));
-    // step y (s = its index in the unrolled block) consumes stage `cur` and
-    // refills it with the loads of step y + PF
-    auto step = [&](Stage &cur, const int s, const int y) {
-        const Raw rw = cur.row;
-        const ST ki_raw = cur.ki, k2i_raw = cur.k2i, k2q_raw = cur.k2q;
-        const IMG im_raw = cur.im;
-        const float cyv = cur.cy;
+    const rsrc_t rout = rsrc(static_cast<ST *>(d.P) + zb);
+    // step y (s = its index in the unrolled block) consumes stage `cur` (row
+    // y + R + 1) and refills it with the row of step y + PF
+    auto step = [&](Raw &cur, const int s, const int y) {
+        const Raw rw = cur;
         // Output y from ring rows y - R .. y + R (slots s .. s + 2R), computed
         // while row y + R + 1 is x-convolved for the next step (also on a
         // chunk's last step: no branch; the row is clamped and zero-padded
         // like any other).  That row is the (y - y0 + 2R + 1)-th staged one:
         // LDS slot parity (y - y0 + 1) & 1.
         auto yconv = [&] {
-            float a = 0.f, b = 0.f;
+            float a = 0.f;
 #pragma unroll
-            for (int k = 0; k < W; ++k) {
-                a = fmaf(tap<R>(t, k), ra[(s + k) % M], a);
-                if (NF == 2) b = fmaf(tap<R>(t, k), rb[(s + k) % M], b);
-            }
-            return make_float2(a, b);
+            for (int k = 0; k < W; ++k) a = fmaf(tap<R>(t, k), ra[(s + k) % M], a);
+            return a;
         };
-        float2 acc, xv;
-        if constexpr (MODE == XY_PAPER2) {
-            // four pointwise inputs per step: interleaving would spill
-            float2 unused;
-            acc = yconv();
-            xv = xrow(rw, y + R + 1, (y - y0 + 1) & 1, nothing, unused);
-        } else {
-            xv = xrow(rw, y + R + 1, (y - y0 + 1) & 1, yconv, acc);
-        }
-        const float acc_a = acc.x, acc_b = acc.y;
-        ra[(s + 2 * R + 1) % M] = xv.x;
-        rb[(s + 2 * R + 1) % M] = xv.y;
-        cur = stage(y + PF);
+        float acc;
+        ra[(s + 2 * R + 1) % M] = xrow(rw, y + R + 1, (y - y0 + 1) & 1, yconv, acc);
+        cur = fetch(y + PF + R + 1);
         // every lane stores: one past the slice edge (x >= nx) writes the
         // value of the last in-slice lane to that lane's element (same bits)
-        const uint32_t v = (uint32_t)(y * g.nx + xc);   // offset within the slice
-        const uint32_t row = (uint32_t)(y * g.nx);
-        auto edge = [&](float val) { return x < g.nx ? val : lane_value(val, last); };
-        if (FITS) {
-            const float ki = to_f(ki_raw);
-            // region fits (Sec. 3 local_intensity)
-            const float K1 = cxz * cyv;
-            const float A2 = ki - acc_a;
-            const float B2 = K1 - acc_b;
-            const float f1 = acc_a * rcp(acc_b);
-            const float f2 = A2 * rcp(B2);
-            if (MODE == XY_PAPER) {
-                // F+- = (I - r+-)^2 (Sec. 4.2 expansion, sigma2 = 0)
-                const float im = to_f(im_raw);
-                const float d1 = im - f1, d2 = im - f2;
-                const float Fd = edge(c.l1 * d1 * d1 - c.l2 * d2 * d2);
-                bst<float>(rout, (uint32_t)xc, Fd, row * 4u);
-                if (probe_fd) probe_fd[zb + v] = Fd;
-            } else if (MODE == XY_PAPER2) {
-                // F+- = K2*I^2 - 2 r+- K2*I + r+-^2 (Sec. 4.2 expansion)
-                const float a = to_f(k2i_raw), q = to_f(k2q_raw);
-                const float F1 = q - 2.f * f1 * a + f1 * f1;
-                const float F2 = q - 2.f * f2 * a + f2 * f2;
-                const float Fd = edge(c.l1 * F1 - c.l2 * F2);
-                bst<float>(rout, (uint32_t)xc, Fd, row * 4u);
-                if (probe_fd) probe_fd[zb + v] = Fd;
-            } else {
-                // force-convolution inputs g1, g2
-                bst_pair<ST>(rout, (uint32_t)xc, edge(c.l1 * f1 - c.l2 * f2),
-                             edge(c.l1 * f1 * f1 - c.l2 * f2 * f2),
-                             row * (uint32_t)sizeof(Pair<ST>));
-            }
-            if (probe_f1) probe_f1[zb + v] = edge(f1);
-            if (probe_f2) probe_f2[zb + v] = edge(f2);
-        } else if (NF == 2) {
-            bst_pair<ST>(rout, (uint32_t)xc, edge(acc_a), edge(acc_b),
-                         row * (uint32_t)sizeof(Pair<ST>));
-        } else {
-            bst<ST>(rout, (uint32_t)xc, from_f<ST>(edge(acc_a)), row * (uint32_t)sizeof(ST));
-        }
+        const float val = x < g.nx ? acc : lane_value(acc, last);
+        bst<ST>(rout, (uint32_t)xc, from_f<ST>(val), (uint32_t)(y * g.nx) * (uint32_t)sizeof(ST));
     };
     // whole blocks of M steps with no branch around the steps (as in the
     // update pass), then the rest of the chunk with a per-step check
@@ -520,9 +375,7 @@ __device__ __forceinline__ void normal_flux(float gx, float gy, float gz, float 
 // of the next z_heaviside pass.  At step z it pushes slice z and emits output
 // slice z - R; R more steps past the end push the zero padding.  The
 // products and the tap order are those of z_heaviside, so P is bitwise the
-// same.  With the RSF force P is also this pass's stage-2 input; the z
-// Gaussian reads P only in the thread's own column, and slice z - R entered
-// the register ring steps before it is overwritten.
+// same.
 template <int R, bool PROBE, class ST, class IT, bool PAPER = false, bool FUSE = false>
 __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t, Coeffs ua)
 {
@@ -547,7 +400,7 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
     // leaves; its partial is not read)
     if (glb(d.flags)[0]) return;
     const Grid3 g = d.g;
-    const gptr<const Pair<ST>> tp = glb(static_cast<const Pair<ST> *>(d.P));
+    const gptr<const Pair<ST>> tp = glb(static_cast<const Pair<ST> *>(d.Q));
     const int cur = glb(d.flags)[1] & 1;   // iterate n is in phi[n & 1]
     const gptr<const float> phi = glb(d.phi[cur]);
     const gptr<float> phi_out = glb(d.phi[cur ^ 1]);
@@ -937,29 +790,10 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
 // ---------------------------------------------------------------------------
 
 template <int R, class IT, class ST>
-hipError_t launch_xy_r(int mode, const Batch &b, int64_t blocks, const Taps &t, const Coeffs &c,
-                       bool, hipStream_t s)
+hipError_t launch_xy_one_r(const Batch &b, int64_t blocks, const Taps &t, const Coeffs &c,
+                           hipStream_t s)
 {
-    const dim3 grid((unsigned)blocks);
-    switch (mode) {
-    case XY_ONE:
-        hipLaunchKernelGGL((xy_kernel<R, XY_ONE, IT, ST>), grid, dim3(64), 0, s, b, t, c);
-        break;
-    case XY_TWO:
-        hipLaunchKernelGGL((xy_kernel<R, XY_TWO, ST, ST>), grid, dim3(64), 0, s, b, t, c);
-        break;
-    case XY_FITS:
-        hipLaunchKernelGGL((xy_kernel<R, XY_FITS, ST, ST>), grid, dim3(64), 0, s, b, t, c);
-        break;
-    case XY_PAPER:
-        hipLaunchKernelGGL((xy_kernel<R, XY_PAPER, ST, ST, IT>), grid, dim3(64), 0, s, b, t, c);
-        break;
-    case XY_PAPER2:
-        hipLaunchKernelGGL((xy_kernel<R, XY_PAPER2, ST, ST, IT>), grid, dim3(64), 0, s, b, t, c);
-        break;
-    default:
-        return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((xy_one_kernel<R, IT, ST>), dim3((unsigned)blocks), dim3(64), 0, s, b, t, c);
     return hipGetLastError();
 }
 
@@ -969,6 +803,36 @@ hipError_t launch_z_plain_r(const Batch &b, int64_t blocks, const Taps &t, int t
 {
     hipLaunchKernelGGL((z_plain_kernel<R, ST>), dim3((unsigned)blocks), dim3(kThreads), 0, s, b, t,
                        target);
+    return hipGetLastError();
+}
+
+// The iteration's xy pass (mode XY_RSF, XY_PAPER or XY_PAPER2).  Probes run
+// with the smaller workgroups.
+template <int R, class IT, class ST>
+hipError_t launch_xyf_r(int mode, const Batch &b, int64_t blocks, int nw, int threads, const Taps &t,
+                        const Coeffs &c, bool probe, hipStream_t s)
+{
+    if (threads < 64 || threads > 64 * nw || threads % 64) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block((unsigned)threads);
+#define RSF_XYF(MODE, PROBE, NW) \
+    hipLaunchKernelGGL((xyf_kernel<R, MODE, PROBE, NW, ST, IT>), grid, block, 0, s, b, t, c)
+    if (nw == 8) {
+        if (mode != XY_RSF || probe) return hipErrorInvalidValue;
+        RSF_XYF(XY_RSF, false, 8);
+    } else if (nw != 4) {
+        return hipErrorInvalidValue;
+    } else if (mode == XY_RSF) {
+        if (probe) RSF_XYF(XY_RSF, true, 4);
+        else RSF_XYF(XY_RSF, false, 4);
+    } else if (mode == XY_PAPER) {
+        if (probe) RSF_XYF(XY_PAPER, true, 4);
+        else RSF_XYF(XY_PAPER, false, 4);
+    } else if (mode == XY_PAPER2) {
+        RSF_XYF(XY_PAPER2, true, 4);   // (rarely used: one instance, whose probes are null)
+    } else {
+        return hipErrorInvalidValue;
+    }
+#undef RSF_XYF
     return hipGetLastError();
 }
 
@@ -1039,8 +903,11 @@ hipError_t launch_z_update_fused_r(const Batch &b, int64_t blocks, const Taps &t
 
 // Instantiate every pass launcher for radius RR, image type IT, storage ST.
 #define RSF_INSTANTIATE(RR, IT, ST)                                                           \
-    template hipError_t launch_xy_r<RR, IT, ST>(int, const Batch &, int64_t, const Taps &,    \
-                                                const Coeffs &, bool, hipStream_t);           \
+    template hipError_t launch_xy_one_r<RR, IT, ST>(const Batch &, int64_t, const Taps &,     \
+                                                    const Coeffs &, hipStream_t);             \
+    template hipError_t launch_xyf_r<RR, IT, ST>(int, const Batch &, int64_t, int, int,       \
+                                                 const Taps &, const Coeffs &, bool,          \
+                                                 hipStream_t);                                \
     template hipError_t launch_z_plain_r<RR, ST>(const Batch &, int64_t, const Taps &, int,   \
                                                  hipStream_t);                                \
     template hipError_t launch_z_heaviside_r<RR, IT, ST>(const Batch &, int64_t, const Taps &, \

@@ -334,8 +334,9 @@ bool launch_chunk(rsf_server *s, std::string &why)
         Taps taps2;
         Coeffs c;
         int iters;
-        View run_xy, run_z, run_u, run_tile, new_xy, new_z, new_tile, fin_z;
+        View run_f, run_z, run_u, run_tile, new_xy, new_z, new_tile, fin_z;
         int n_new, n_run, n_fin;
+        XyfShape shape_f;
         bool fuse;
     };
     std::vector<Launch> launches;
@@ -386,18 +387,23 @@ bool launch_chunk(rsf_server *s, std::string &why)
                 p.push_back(p.back() + (int)blocks(d[i].g, d[i].sp));
             return p;
         };
-        const std::vector<int> rxy = prefix(drun, 0, rsf::xy_blocks),
-                               rz = prefix(drun, 0, rsf::z_blocks),
+        std::vector<Grid3> grids;
+        for (const TileDesc &d : drun) grids.push_back(d.g);
+        const XyfShape shape_f = xyf_shape(grids, gp->req.params.force, gp->R, false);
+        std::vector<int> rf(1, 0);
+        for (const TileDesc &d : drun) rf.push_back(rf.back() + (int)rsf::xyf_blocks(d.g, d.sp, shape_f.halo,
+                                                                                  shape_f.nw));
+        const std::vector<int> rz = prefix(drun, 0, rsf::z_blocks),
                                ru = prefix(drun, 0, rsf::u_blocks),
                                nxy = prefix(drun, n_old, rsf::xy_blocks),
                                nz = prefix(drun, n_old, rsf::z_blocks),
                                fz = prefix(dfin, 0, rsf::z_blocks);
         const size_t o_run = drun.empty() ? 0 : tw.put(drun.data(), drun.size());
         const size_t o_fin = dfin.empty() ? 0 : tw.put(dfin.data(), dfin.size());
-        const size_t o_rxy = tw.put(rxy.data(), rxy.size()), o_rz = tw.put(rz.data(), rz.size()),
+        const size_t o_rf = tw.put(rf.data(), rf.size()), o_rz = tw.put(rz.data(), rz.size()),
                      o_ru = tw.put(ru.data(), ru.size()), o_nxy = tw.put(nxy.data(), nxy.size()),
                      o_nz = tw.put(nz.data(), nz.size()), o_fz = tw.put(fz.data(), fz.size());
-        for (size_t o : {o_run, o_fin, o_rxy, o_rz, o_ru, o_nxy, o_nz, o_fz})
+        for (size_t o : {o_run, o_fin, o_rf, o_rz, o_ru, o_nxy, o_nz, o_fz})
             if (o == (size_t)-1) {
                 why = "tile table overflow";
                 return false;
@@ -431,10 +437,11 @@ bool launch_chunk(rsf_server *s, std::string &why)
                 gs.push_back(d[i].g);
                 sps.push_back(d[i].sp);
             }
-            v.blocks = balance_xcds(v.b, k, gs, sps, L.R);
+            v.blocks = balance_xcds(v.b, k, gs, sps, L.R, shape_f.halo, shape_f.nw);
             return v;
         };
-        L.run_xy = view(dr, drun, 0, o_rxy, PASS_XY);
+        L.shape_f = shape_f;
+        L.run_f = view(dr, drun, 0, o_rf, PASS_F);
         L.run_z = view(dr, drun, 0, o_rz, PASS_Z);
         L.run_u = view(dr, drun, 0, o_ru, PASS_U);
         L.run_tile = View{Batch{dr, nullptr, L.n_run, {}}, L.n_run};
@@ -482,8 +489,8 @@ bool launch_chunk(rsf_server *s, std::string &why)
                 Coeffs sq = L.c;
                 for (int k = 0; k < 2; ++k) {
                     sq.square = k;
-                    if (!ok(rsf::launch_xy(L.R2, rsf::XY_ONE, L.image, L.storage, L.new_xy.b,
-                                           L.new_xy.blocks, L.taps2, sq, false, st),
+                    if (!ok(rsf::launch_xy_one(L.R2, L.image, L.storage, L.new_xy.b,
+                                               L.new_xy.blocks, L.taps2, sq, st),
                             "K2*I (xy)") ||
                         !ok(rsf::launch_z_plain(L.R2, L.storage, L.new_z.b, L.new_z.blocks,
                                                 L.taps2, k ? rsf::Z_TO_K2I2 : rsf::Z_TO_K2I, st),
@@ -491,8 +498,8 @@ bool launch_chunk(rsf_server *s, std::string &why)
                         return false;
                 }
             }
-            if (!ok(rsf::launch_xy(L.R, rsf::XY_ONE, L.image, L.storage, L.new_xy.b,
-                                   L.new_xy.blocks, L.taps, L.c, false, st),
+            if (!ok(rsf::launch_xy_one(L.R, L.image, L.storage, L.new_xy.b,
+                                       L.new_xy.blocks, L.taps, L.c, st),
                     "K*I (xy)"))
                 return false;
             if (!ok(rsf::launch_z_plain(L.R, L.storage, L.new_z.b, L.new_z.blocks, L.taps,
@@ -511,14 +518,11 @@ bool launch_chunk(rsf_server *s, std::string &why)
             if ((!L.fuse && !ok(rsf::launch_z_heaviside(L.R, L.image, L.storage, L.run_z.b,
                                                         L.run_z.blocks, L.taps, L.c, false, st),
                                 "z(H)")) ||
-                !ok(rsf::launch_xy(L.R,
-                                   paper ? (L.k2 ? rsf::XY_PAPER2 : rsf::XY_PAPER) : rsf::XY_FITS,
-                                   L.image, L.storage, L.run_xy.b, L.run_xy.blocks, L.taps, L.c,
-                                   false, st),
-                    "xy(fits)") ||
-                (!paper && !ok(rsf::launch_xy(L.R, rsf::XY_TWO, L.image, L.storage, L.run_xy.b,
-                                              L.run_xy.blocks, L.taps, L.c, false, st),
-                               "xy(g)")) ||
+                !ok(rsf::launch_xyf(L.R,
+                                    paper ? (L.k2 ? rsf::XY_PAPER2 : rsf::XY_PAPER) : rsf::XY_RSF,
+                                    L.image, L.storage, L.run_f.b, L.run_f.blocks, L.shape_f.nw,
+                                    L.shape_f.threads, L.taps, L.c, false, st),
+                    "xy") ||
                 !ok(L.fuse ? rsf::launch_z_update_fused(L.R, L.image, L.storage, L.run_u.b,
                                                         L.run_u.blocks, L.taps, L.c, paper, st)
                     : paper ? rsf::launch_z_update_paper(L.image, L.storage, L.run_u.b,

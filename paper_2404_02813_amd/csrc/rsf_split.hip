@@ -28,6 +28,8 @@ Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_t
     s.xy = chunks(g.ny, strips * g.nz, xy_waves, 8);
     s.z = chunks(g.nz, z_cols(g), z_target, 8);
     s.u = chunks(g.nz, (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy), u_target, 8);
+    // an xy-pass workgroup holds several waves and pays a halo of up to 4 R rows
+    s.f = chunks(g.ny, (int64_t)xyf_strips(g.nx, 9, xyf_waves(g.nx, 9)).n * g.nz, xy_waves / 16, 32);
     return s;
 }
 
@@ -76,11 +78,38 @@ static int capacity_chunks(int64_t nz, int64_t cols, int64_t resident, double mi
     return (int)((nz + len - 1) / len);
 }
 
-Split capacity_split(const Grid3 &g, int R)
+XyfPick xyf_pick(const Grid3 &g, int R, int halo)
+{
+    XyfPick best{4, 1};
+    double least = -1.0;
+    const int reach = 2 * (R + halo);   // R (+ R with two stages) above and below
+    for (int nw = 4; nw <= (halo > 0 ? 8 : 4); nw += 4) {
+        const XyfStrips st = xyf_strips(g.nx, halo, nw);
+        const int waves = (st.width + 63) / 64;
+        const int64_t slots = resident_f(R, nw, waves) / kCus;
+        for (int c = 1; c <= (g.ny + 3) / 4; ++c) {
+            const int len = (g.ny + c - 1) / c;
+            if ((g.ny + len - 1) / len != c) continue;
+            const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
+            const int64_t at_once = std::min(per_cu, slots);
+            const double load = std::max(1.5, 0.25 * (double)(at_once * waves));
+            const int rows = len + (c == 1 ? 0 : c == 2 ? reach / 2 : reach) + 8;
+            const double cost = (double)((per_cu + at_once - 1) / at_once) * rows * load;
+            if (least < 0.0 || cost < 0.97 * least) {
+                least = cost;
+                best = XyfPick{nw, c};
+            }
+        }
+    }
+    return best;
+}
+
+Split capacity_split(const Grid3 &g, int R, int halo)
 {
     Split s = default_split(g, 1.0, kDefaultTargets);
     // a z-pass chunk primes its ring with 2R slices; an update chunk reads R
     // extra slices of the pair ring on average and 4 of phi
+    s.f = xyf_pick(g, R, halo).f;
     s.z = capacity_chunks(g.nz, z_cols(g), kResidentZ, 0.5, 2 * R);
     s.u = capacity_chunks(g.nz, (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy),
                           kResidentU, 0.75, R + 2);
@@ -96,7 +125,7 @@ static bool chunks_ok(int n, int c)
 
 bool split_valid(const Grid3 &g, const Split &s)
 {
-    return chunks_ok(g.ny, s.xy) && chunks_ok(g.nz, s.z) && chunks_ok(g.nz, s.u) &&
+    return chunks_ok(g.ny, s.xy) && chunks_ok(g.nz, s.z) && chunks_ok(g.nz, s.u) && chunks_ok(g.ny, s.f) &&
            u_blocks(g, s) <= u_blocks_max(g);
 }
 

@@ -1,0 +1,427 @@
+// The xy pass of an iteration: both Gaussian stages' x and y convolutions of
+// one z slice, with the region fits between them, in one kernel (RSF force),
+// or the one stage of the Sec. 4.2 force with its pointwise epilogue.
+#pragma once
+
+#include <type_traits>
+#include <utility>
+
+#include "rsf_device.hpp"
+
+namespace rsf {
+
+namespace {
+
+template <int I>
+using ic = std::integral_constant<int, I>;
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(ic<I>{}), ...);
+}
+// f(ic<0>), ..., f(ic<N - 1>): indices that reach an instruction as immediates
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+template <class F, int... I>
+__device__ __forceinline__ bool all_of_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    return (f(ic<I>{}) && ...);
+}
+
+using f4 = float __attribute__((ext_vector_type(4)));
+using f4u = float __attribute__((ext_vector_type(4), aligned(4)));
+
+// The 2R + 1 taps as operands of v_mfma_f32_4x4x1 (16 blocks of a 4 x 4 outer
+// product; lane l is column l % 4 of block l / 4 as operand B and row l % 4
+// as operand A).  Four consecutive outputs of a convolution take one input
+// element with four consecutive taps: pattern p holds w[p - 3 + 0..3], zero
+// outside 0..2R, for p = 0 .. 2R + 3.
+//   y: operand A, block b of register q is pattern 16 q + b; the instruction
+//      broadcasts one block to all (cbsz 4, abid b), so every lane's column
+//      receives the same four taps.
+//   x: operand B, 16-lane group g of register q is the pattern of input
+//      4 q + g (w[k - 0..3], the mirrored one), broadcast by blgp 4 + g.
+template <int R>
+struct TapOps {
+    static constexpr int N = 2 * R + 4;
+    float y[(N + 15) / 16], x[(N + 3) / 4];
+    __device__ __forceinline__ void load(const Taps &t, int lane)
+    {
+        auto w = [&](int i) { return i >= 0 && i <= 2 * R ? t.w[min(max(i, 0), 2 * R)] : 0.f; };
+#pragma unroll
+        for (int q = 0; q < (N + 15) / 16; ++q) y[q] = w(16 * q + lane / 4 - 3 + lane % 4);
+#pragma unroll
+        for (int q = 0; q < (N + 3) / 4; ++q) x[q] = w(4 * q + lane / 16 - lane % 4);
+    }
+};
+
+// Raw buffer of exactly `bytes` (at most 2 GiB): a load at an offset outside
+// it returns 0, a store is dropped.  Rows above or below the slice (offsets
+// that are negative, hence huge, or past its end) are then the zero padding
+// with no mask, and a lane with nothing to load or store sets the top bit of
+// its offset.
+constexpr uint32_t kOut = 0x80000000u;
+__device__ __forceinline__ rsrc_t rsrc_n(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes,
+                                             kRsrcFlags);
+}
+template <class T>
+__device__ __forceinline__ T bld_at(rsrc_t r, uint32_t off)
+{
+    if constexpr (sizeof(T) == 2)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0));
+    else if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+template <class T>
+__device__ __forceinline__ void bst_at(rsrc_t r, uint32_t off, T v)
+{
+    if constexpr (sizeof(T) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, off, 0, 0);
+    } else {
+        static_assert(sizeof(T) == 8, "4 or 8-byte elements");
+        using U2 = unsigned int __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, off, 0, 0);
+    }
+}
+
+// A workgroup owns a strip of at most 64 NW columns of one slice (64 per
+// wave) and a chunk of rows, and marches down it four rows per step.  Step G:
+//   - rows of group G (with an R halo in x) are in LDS; each lane x-convolves
+//     them for its column (operand A: lane 4 b + i reads row i from column
+//     4 b; the result's register is the row, its lane the column);
+//   - each of the four x-convolved rows is added into the sums of every
+//     output row it reaches (y): NG groups of four rows are open at a time,
+//     the oldest of which is complete at the end of the step;
+//   - its region fits give g1, g2 of four rows, which go to LDS and are
+//     convolved the same way in step G + 1 (RSF force), or the force of
+//     Sec. 4.2, which is stored.
+// Rows of group G + 1 are written to the other LDS buffer and those of G + 2
+// loaded meanwhile; one barrier per step.
+template <int R, int MODE, bool PROBE, int NW, class ST, class IMG>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(R <= 9 ? 3 : 2)))
+void xyf_kernel(Batch bt, Taps t, Coeffs c)
+{
+    constexpr bool TWO = MODE == XY_RSF;
+    constexpr int NG = (2 * R + 3) / 4 + 1;          // open output groups
+    constexpr int NK = TapOps<R>::N, NQ = (NK + 3) / 4;
+    // a staged row: columns -R .. 64 * waves + R, read in 16-byte pieces up to
+    // 4 * NQ - 4 past the last column's piece.  Row stride 16 or 48 mod 64
+    // words: the 16-byte reads of 16 consecutive lanes (4 rows x 4 columns)
+    // then fall on all 64 banks.
+    constexpr int need = (64 * NW) + 4 * NQ;
+    constexpr int S = need + ((16 - need % 64 + 64) % 64 < (48 - need % 64 + 64) % 64
+                                  ? (16 - need % 64 + 64) % 64
+                                  : (48 - need % 64 + 64) % 64);
+    constexpr int BUF = 2 * 4 * S;                   // [field][row][column]
+    __shared__ __attribute__((aligned(16))) float lds[(TWO ? 4 : 2) * BUF];
+
+    Where wh;
+    if (!locate(bt, wh)) return;
+    const TileDesc &d = bt.tiles[wh.t];
+    if (glb(d.flags)[0]) return;
+    const Grid3 g = d.g;
+    const XyfStrips sg = xyf_strips(g.nx, MODE == XY_RSF ? R : 0, NW);
+    const int strip = wh.lb % sg.n, rest = wh.lb / sg.n;
+    const int yc = rest % d.sp.f, z = rest / d.sp.f;
+    const int ly = (g.ny + d.sp.f - 1) / d.sp.f;
+    const int y0 = yc * ly, y1 = min(y0 + ly, g.ny);
+    constexpr int H = TWO ? R : 0;                   // columns a strip shares with the next
+    const int c0 = min(strip * sg.step, g.nx - sg.width);   // first column of the strip
+    const int nw = (sg.width + 63) / 64;             // its waves
+    for (int i = threadIdx.x; i < (TWO ? 4 : 2) * BUF; i += (int)blockDim.x) lds[i] = 0.f;
+    __syncthreads();
+    // Waves past the strip leave.  Which of the workgroup's waves these are
+    // turns with the workgroup, so that no SIMD is left with fewer waves.
+    const int waves = (int)blockDim.x / 64;
+    const int wave = ((int)__builtin_amdgcn_readfirstlane(threadIdx.x / 64) + wh.lb) % waves;
+    if (wave >= nw) return;
+    const int tid = 64 * wave + (int)(threadIdx.x & 63);
+
+    const int lane = tid & 63;
+    const int64_t zb = (int64_t)z * g.sxy;
+    const int x = c0 + tid;
+    const bool xin = x < g.nx;
+    constexpr uint32_t PB = sizeof(Vec2<ST>);
+    TapOps<R> tp;
+    tp.load(t, lane);
+
+    const uint32_t plane = (uint32_t)g.sxy, nx = (uint32_t)g.nx;
+    constexpr uint32_t SB = sizeof(ST), IB = sizeof(IMG);
+    const rsrc_t rin = rsrc_n(static_cast<const char *>(d.P) + zb * (int64_t)PB, plane * PB);
+    const rsrc_t rki = rsrc_n(static_cast<const ST *>(d.KI) + zb, plane * SB);
+    const rsrc_t rim = rsrc_n(static_cast<const IMG *>(d.I) + zb, plane * IB);
+    const rsrc_t rk2i = rsrc_n(static_cast<const ST *>(d.K2I) + zb, plane * SB);
+    const rsrc_t rk2q = rsrc_n(static_cast<const ST *>(d.K2I2) + zb, plane * SB);
+    constexpr uint32_t OB = TWO ? PB : 4u;           // bytes of an output element
+    // the chunk's rows only: the output rows of priming steps and past the
+    // chunk's end are dropped
+    const rsrc_t rout = rsrc_n(static_cast<char *>(d.Q) + (zb + (int64_t)y0 * g.nx) * (int64_t)OB,
+                               (uint32_t)(y1 - y0) * nx * OB);
+    // columns this strip stores: all but the halo it shares with a neighbour
+    const int o0 = strip == 0 ? 0 : strip * sg.step + H;
+    const int o1 = strip == sg.n - 1 ? g.nx : c0 + sg.width - H;
+    const uint32_t ibad = xin ? 0u : kOut, obad = x >= o0 && x < o1 ? 0u : kOut;
+    const int xkeep = xin ? -1 : 0;
+    const float cxz = glb(d.cx)[min(x, g.nx - 1)] * glb(d.cz)[z];
+    const float *const cyp = d.cy;
+
+    // x halo of the four rows of a group: thread k < 8 R takes row k / 2R,
+    // halo column k % 2R (left, then right of the strip's 64 nw columns); the
+    // others write to an element of the row's padding that is never read
+    const int hr = tid / (2 * R), hc = tid % (2 * R);
+    const bool has_h = tid < 8 * R;
+    const int hx = hc < R ? c0 - R + hc : c0 + 64 * nw + hc - R;
+    const uint32_t hbad = has_h && hx >= 0 && hx < g.nx ? 0u : kOut;
+    const int hdst = has_h ? hr * S + (hc < R ? hc : 64 * nw + hc) : S - 1;
+    static_assert((64 * NW) + 4 * NQ - 4 <= S - 1, "the padding element is past every read");
+
+    // first input row of group 0, so that the first output row is y0
+    constexpr int PAD = TWO ? 0 : (4 - 2 * R % 4) % 4;
+    const int r0 = y0 - (TWO ? 2 * R : R + PAD);
+    constexpr int GF = TWO ? R + 1 : (2 * R + PAD) / 4;   // step of the first output row
+    const int gend = GF + (y1 - y0 + 3) / 4;
+    // steps before GP complete no row the chunk uses: they only convolve and
+    // sum.  A chunk that starts the volume skips the groups of zeros above it.
+    constexpr int GP = TWO ? 2 * R / 4 : GF, GZ = TWO ? GP : (R + PAD) / 4;
+    static_assert(GZ <= GP, "the loop starts at step GP");
+    int G = y0 > 0 ? 0 : GZ;
+
+    // element offset of row r of n (clamped to one row outside: on planes of
+    // a few very long rows, more would wrap around to valid offsets)
+    auto at_row = [&](int r, int n) { return (uint32_t)min(max(r, -1), n) * nx; };
+    const uint32_t e0 = (uint32_t)x;
+    struct Rows {
+        Vec2<ST> m[4], h;
+    };
+    auto fetch = [&](int grp) {
+        Rows v;
+        const int row = r0 + 4 * grp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v.m[i] = bld_at<Vec2<ST>>(rin, ((e0 + at_row(row + i, g.ny)) * PB) | ibad);
+        v.h = bld_at<Vec2<ST>>(rin, (((uint32_t)hx + at_row(row + hr, g.ny)) * PB) | hbad);
+        return v;
+    };
+    float *const wr = lds + R + tid;                 // own column of row 0
+    auto put = [&](const Rows &v, int buf) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            wr[buf + i * S] = to_f(v.m[i].x);
+            wr[buf + (4 + i) * S] = to_f(v.m[i].y);
+        }
+        lds[buf + hdst] = to_f(v.h.x);
+        lds[buf + hdst + 4 * S] = to_f(v.h.y);
+    };
+    // pointwise inputs of the fits of the group completed in step grp
+    struct Point {
+        ST ki[4], k2i[4], k2q[4];
+        IMG im[4];
+        f4 cy;
+    };
+    auto point = [&](int grp) {
+        Point p;
+        const int rb = r0 - R + 4 * grp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t e = e0 + at_row(rb + i, g.ny);
+            p.ki[i] = bld_at<ST>(rki, e * SB);
+            if constexpr (MODE == XY_PAPER) p.im[i] = bld_at<IMG>(rim, e * IB);
+            if constexpr (MODE == XY_PAPER2) {
+                p.k2i[i] = bld_at<ST>(rk2i, e * SB);
+                p.k2q[i] = bld_at<ST>(rk2q, e * SB);
+            }
+        }
+        // one scalar load; rows outside the table (at most 2 R + 8 entries on
+        // either side) are their neighbours' in the tile's workspace, each at
+        // least 64 entries long, and go nowhere
+        p.cy = *(const __attribute__((address_space(4))) f4u *)(cyp + rb);
+        return p;
+    };
+    const int aoff = (lane & 3) * S + (tid & ~63) + (lane & ~3);
+    // x convolution of the four staged rows of a buffer, both fields; the LDS
+    // reads run one piece (4 columns) ahead of the products
+    auto xconv = [&](int buf, f4 &xa, f4 &xb) {
+        f4 a{}, b{}, va[2], vb[2];
+        const float *const src = lds + buf + aoff;
+        auto read = [&](int q) {
+            va[q & 1] = *reinterpret_cast<const f4 *>(src + 4 * q);
+            vb[q & 1] = *reinterpret_cast<const f4 *>(src + 4 * S + 4 * q);
+        };
+        read(0);
+        static_for<NQ>([&](auto qc) {
+            constexpr int q = qc;
+            if constexpr (q + 1 < NQ) read(q + 1);
+            // (opaque: kept as 16-byte reads)
+            __asm__ volatile("" : "+v"(va[q & 1]), "+v"(vb[q & 1]));
+            static_for<4>([&](auto kc) {
+                constexpr int k = kc;
+                if constexpr (4 * q + k < NK) {
+                    a = __builtin_amdgcn_mfma_f32_4x4x1f32(va[q & 1][k], tp.x[q], a, 0, 0, 4 + k);
+                    b = __builtin_amdgcn_mfma_f32_4x4x1f32(vb[q & 1][k], tp.x[q], b, 0, 0, 4 + k);
+                }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        xa = a;
+        xb = b;
+    };
+    // add the four rows to the open groups (group m of the step in slot
+    // (T + m) % NG; group NG - 1 starts here), rows in order
+    auto ysum = [&](auto T, f4 *sa, f4 *sb, const f4 &xa, const f4 &xb) {
+        static_for<4>([&](auto ci) {
+            static_for<NG>([&](auto cm) {
+                constexpr int i = ci, m = cm;
+                constexpr int p = 4 * m - i + 3;     // tap pattern
+                if constexpr (p >= 0 && p < NK) {
+                    constexpr int s = (T + m) % NG;
+                    // the first row that reaches the newest group
+                    constexpr bool first = m == NG - 1 && (i == 0 || p + 1 >= NK);
+                    const f4 zero{};
+                    sa[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[p / 16], xa[i],
+                                                               first ? zero : sa[s], 4, p % 16, 0);
+                    sb[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[p / 16], xb[i],
+                                                               first ? zero : sb[s], 4, p % 16, 0);
+                }
+            });
+        });
+        // opaque, or the compiler would sink sums to the step that completes
+        // them and keep their inputs instead
+#pragma unroll
+        for (int m = 0; m < NG; ++m) __asm__ volatile("" : "+v"(sa[m]), "+v"(sb[m]));
+    };
+
+    f4 a1[NG], b1[NG], a2[TWO ? NG : 1], b2[TWO ? NG : 1];
+#pragma unroll
+    for (int m = 0; m < NG; ++m) a1[m] = b1[m] = f4{};
+    if constexpr (TWO) {
+#pragma unroll
+        for (int m = 0; m < NG; ++m) a2[m] = b2[m] = f4{};
+    }
+    const gptr<float> probe_f1 = glb(d.probe_f1), probe_f2 = glb(d.probe_f2),
+                      probe_fd = glb(d.probe_Fd);
+    int cur = 0;                                     // LDS buffer of group G
+    put(fetch(G), cur);
+    Rows nxt = fetch(G + 1);
+
+    Point pt;
+    int oth = BUF;
+    // stage 1 of step G; the fits' inputs are loaded here and used after it
+    auto stage1 = [&](auto T, auto fits) {
+        // opaque, or the compiler would keep every LDS address of both
+        // buffers in a register
+        __asm__ volatile("" : "+s"(cur));
+        oth = BUF - cur;
+        __asm__ volatile("" : "+s"(oth));
+        __syncthreads();
+        put(nxt, oth);
+        if constexpr (fits) pt = point(G);
+        nxt = fetch(G + 2);
+        f4 xa, xb;
+        xconv(cur, xa, xb);
+        ysum(T, a1, b1, xa, xb);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto prime = [&](auto j) {   // (the loop below starts in slot 0)
+        G = j;
+        stage1(ic<((j - GP) % NG + NG) % NG>{}, std::false_type{});
+        cur = oth;
+    };
+    if (y0 > 0) static_for<GP>(prime);
+    else static_for<GP - GZ>([&](auto j) { prime(ic<j + GZ>{}); });
+    G = GP;
+
+    auto step = [&](auto T) -> bool {
+        stage1(T, std::true_type{});
+        const f4 A = a1[T], B = b1[T];
+        const int rb = r0 - R + 4 * G;               // rows of the completed group
+        float u[4], v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // region fits (Sec. 3 local_intensity)
+            const float K1 = cxz * pt.cy[i];
+            const float A2 = to_f(pt.ki[i]) - A[i];
+            const float B2 = K1 - B[i];
+            const float f1 = A[i] * rcp(B[i]);
+            const float f2 = A2 * rcp(B2);
+            if constexpr (MODE == XY_PAPER) {
+                // F+- = (I - r+-)^2 (Sec. 4.2 expansion, sigma2 = 0)
+                const float im = to_f(pt.im[i]);
+                const float d1 = im - f1, d2 = im - f2;
+                u[i] = c.l1 * d1 * d1 - c.l2 * d2 * d2;
+            } else if constexpr (MODE == XY_PAPER2) {
+                // F+- = K2*I^2 - 2 r+- K2*I + r+-^2 (Sec. 4.2 expansion)
+                const float a = to_f(pt.k2i[i]), q = to_f(pt.k2q[i]);
+                const float F1 = q - 2.f * f1 * a + f1 * f1;
+                const float F2 = q - 2.f * f2 * a + f2 * f2;
+                u[i] = c.l1 * F1 - c.l2 * F2;
+            } else {
+                // inputs of the force convolution; zero outside the volume
+                // (the row's mask opaque: a select would go through VCC)
+                int rk = ~(((rb + i) | (g.ny - 1 - rb - i)) >> 31);
+                __asm__ volatile("" : "+s"(rk));
+                const int keep = xkeep & rk;
+                float g1 = c.l1 * f1 - c.l2 * f2, g2 = c.l1 * f1 * f1 - c.l2 * f2 * f2;
+                if constexpr (!std::is_same<ST, float>::value) {
+                    // rounded to FP32, then to the storage type (opaque: not
+                    // in one step), as every field of an iteration is
+                    pin(g1);
+                    pin(g2);
+                    g1 = to_f(from_f<ST>(g1));
+                    g2 = to_f(from_f<ST>(g2));
+                }
+                u[i] = __int_as_float(__float_as_int(g1) & keep);
+                v[i] = __int_as_float(__float_as_int(g2) & keep);
+            }
+            if constexpr (PROBE) {
+                if (rb + i >= y0 && rb + i < y1 && x >= o0 && x < o1) {
+                    const int64_t at = zb + (int64_t)(rb + i) * g.nx + x;
+                    if (probe_f1) probe_f1[at] = f1;
+                    if (probe_f2) probe_f2[at] = f2;
+                    if (!TWO && probe_fd) probe_fd[at] = u[i];
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TWO) {
+            // this step's g into the other buffer; the previous step's is
+            // convolved
+            float *const wg = wr + 2 * BUF + oth;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                wg[i * S] = u[i];
+                wg[(4 + i) * S] = v[i];
+            }
+            f4 ga, gb;
+            xconv(2 * BUF + cur, ga, gb);
+            ysum(T, a2, b2, ga, gb);
+        }
+        const int orow = TWO ? rb - R - 4 - y0 : rb - y0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t off = ((e0 + at_row(orow + i, y1 - y0)) * OB) | obad;
+            if constexpr (TWO) {
+                Vec2<ST> w;
+                w.x = from_f<ST>(a2[T][i]);
+                w.y = from_f<ST>(b2[T][i]);
+                bst_at<Vec2<ST>>(rout, off, w);
+            } else {
+                bst_at<float>(rout, off, u[i]);
+            }
+        }
+        cur = oth;
+        return ++G < gend;
+    };
+    while (all_of_impl(step, std::make_integer_sequence<int, NG>{})) {
+    }
+}
+
+}  // namespace
+
+}  // namespace rsf
