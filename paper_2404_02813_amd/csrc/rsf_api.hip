@@ -1761,7 +1761,7 @@ rsf_status seeds_impl(rsf_context *ctx, Scratch &sc, const void *volume, int vdt
 rsf_status sweep_impl(rsf_context *ctx, float *u, int64_t nx, int64_t ny, int64_t nz, int rounds,
                       hipStream_t s)
 {
-    const int64_t planes = rsf::sweep_block_planes(nx, ny, nz);
+    const int64_t planes = rsf::sweep_wavefronts(nx, ny, nz);
     for (int r = 0; r < rounds; ++r)
         for (int dir = 0; dir < 8; ++dir)
             for (int64_t h = 0; h < planes; ++h)

@@ -295,100 +295,179 @@ __global__ __launch_bounds__(kThreads) void seeds_kernel(const float *dohp, cons
 }
 
 // Godunov update of |grad u| = 1 on the unit grid from the smallest
-// neighbour value along each axis (a, b, c; kFar when absent).  The roots
+// neighbour value along each axis (x, y, z; kFar when absent).  The roots
 // are written in the differences d1 = b - a, d2 = c - a, which are O(1)
 // where they are used: the textbook discriminant (a+b+c)^2 - 3(a^2+b^2+c^2-1)
 // cancels to O(1) from O(u^2) terms and loses most FP32 digits at large u.
-__device__ __forceinline__ float godunov(float a, float b, float c)
+// All three candidates are computed (their chains overlap) and one selected;
+// the others may be NaN.
+// sqrt correctly rounded, for a normal x (here 0.03..3: the library's scaling
+// of denormal and huge arguments is left out; others give some value that is
+// not used): the hardware root, within an ulp, moved to the neighbour that a
+// Tuckerman test of the residuals selects.
+__device__ __forceinline__ float sqrt_normal(float x)
 {
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float lo = __int_as_float(__float_as_int(s) - 1);
+    const float hi = __int_as_float(__float_as_int(s) + 1);
+    float r = fmaf(-lo, s, x) <= 0.f ? lo : s;
+    if (fmaf(-hi, s, x) > 0.f) r = hi;
+    return r;
+}
+// The smaller of two values, or the one that is a number (as fminf; one
+// instruction, where fminf first quiets operands that come from memory).
+__device__ __forceinline__ float min_num(float x, float y)
+{
+    float r;
+    __asm__("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+__device__ __forceinline__ float godunov(float &a, float b, float c)
+{
+    // sorted by comparisons (not min/max, which would drop a NaN)
     float t;
     if (a > b) { t = a; a = b; b = t; }
     if (b > c) { t = b; b = c; c = t; }
     if (a > b) { t = a; a = b; b = t; }
-    if (a + 1.f <= b) return a + 1.f;
     const float d1 = b - a;
-    const float r2 = 0.5f * (d1 + sqrtf(2.f - d1 * d1));
-    if (a + r2 <= c) return a + r2;
+    const float r2 = 0.5f * (d1 + sqrt_normal(2.f - d1 * d1));
     const float d2 = c - a, d3 = d2 - d1;
-    return a + (d1 + d2 + sqrtf(3.f - (d1 * d1 + d2 * d2 + d3 * d3))) * (1.f / 3.f);
+    const float v3 =
+        a + (d1 + d2 + sqrt_normal(3.f - (d1 * d1 + d2 * d2 + d3 * d3))) * (1.f / 3.f);
+    return a + 1.f <= b ? a + 1.f : (a + r2 <= c ? a + r2 : v3);
 }
 
-// One hyperplane of blocks of a sweep.  In the sweep's orientation
-// (i' = i or nx-1-i by its x order, likewise j', k') the volume is cut into
-// blocks of kSbx x kSby x kSbz; the blocks with bi' + bj' + bk' = H are
-// independent: a block's upwind neighbours (i'-1, j'-1, k'-1 across a face)
-// lie in blocks of hyperplane H-1, already swept, and its downwind ones in
-// hyperplane H+1, not yet.  One wave loads its block with a one-voxel face
-// halo into LDS (absent points as kFar), marches the block's own inner
-// hyperplanes in order (lane = one (j', k') line) and writes the block back.
-// Every point is thus updated after its upwind neighbours and before its
-// downwind ones, which gives exactly the sequential Gauss-Seidel sweep.
-// Workgroup g covers bj' = g % nby, bk' = kblo + g / nby.
-constexpr int kSbx = 32, kSby = 8, kSbz = 8;
-static_assert(kSby * kSbz == 64, "one lane per (j', k') line of a block");
-__global__ __launch_bounds__(64) void sweep_block_kernel(float *up, int64_t nx, int64_t ny,
-                                                         int64_t nz, int dir, int64_t H,
-                                                         int64_t nbx, int64_t nby, int64_t kblo)
+// One wavefront of blocks of a sweep.  In the sweep's orientation (i' = i or
+// nx-1-i by its x order, likewise j', k') the points of a hyperplane
+// s = i' + j' + k' do not depend on each other: each needs its upwind
+// neighbours (s - 1) as already swept and its downwind ones (s + 1) as not
+// yet.  A block is kSj x kSj lines (j', k') times kSs consecutive hyperplanes,
+// so in the skewed coordinates (s; j', k') it needs the blocks (b - 1; J, K),
+// (b; J - 1, K) and (b; J, K - 1) before it, and the blocks with
+// b + J + K = W form one launch.  Every point is updated after its upwind
+// neighbours and before its downwind ones, which gives exactly the sequential
+// Gauss-Seidel sweep.
+//
+// The block's lines and one line around them are loaded skewed, [s][k'][j'],
+// kSs + 2 planes (absent points as kFar); thread (j', k') updates its point of
+// one plane after the other, one barrier each, and a block that changed is
+// written back.
+//
+// What bounds it is the chain of dependent steps: (nx + ny + nz) / kSs +
+// (ny + nz) / kSj launches a sweep, each a block's load, kSs steps and its
+// store.  512^3, 2 rounds: 1760 launches of 21 us, 103 -> 43 ms a call;
+// unskewed blocks of 32 x 8 x 8, whose 46 inner hyperplanes are mostly idle,
+// took 2272 launches of 43 us.  The wave runs alone on its SIMD and issues an
+// instruction every 5 to 6 clocks, so instructions count, not operations:
+// dividing out each element's coordinates while staging cost 38 us a launch.
+constexpr int kSj = 16, kSs = 32;
+__global__ __launch_bounds__(kSj * kSj) void sweep_block_kernel(float *up, int nx, int ny, int nz,
+                                                                int dir, int W, int nb, int nbj,
+                                                                int kblo)
 {
-    constexpr int TX = kSbx + 2, TY = kSby + 2, TZ = kSbz + 2;
-    __shared__ float tile[TZ][TY][TX];
-    const int64_t gb = blockIdx.x;
-    const int64_t bj = gb % nby, bk = kblo + gb / nby;
-    const int64_t bi = H - bj - bk;
-    if (bi < 0 || bi >= nbx) return;   // the whole workgroup
+    constexpr int T = kSj + 2, NT = kSj * kSj;
+    constexpr int PL = T * T + 1;   // plane pitch, odd: the skewed writes spread over the banks
+    static_assert(kSs == 32 && NT == 256, "eight half-waves, each a line's 32 planes");
+    __shared__ float tile[(kSs + 2) * PL];
+    __shared__ int any;
+    const int bj = (int)blockIdx.x % nbj, bk = kblo + (int)blockIdx.x / nbj;
+    const int b = W - bj - bk;
+    const int j0 = bj * kSj, k0 = bk * kSj, s0 = b * kSs;   // oriented origin
+    if (b < 0 || b >= nb) return;                           // the whole workgroup
+    // hyperplanes of the block's lines: none of this block's kSs, no work
+    const int lo = j0 + k0, hi = min(j0 + kSj, ny) - 1 + min(k0 + kSj, nz) - 1 + nx - 1;
+    if (s0 + kSs <= lo || s0 > hi) return;
+    const int tid = threadIdx.x;
     const gptr<float> u = glb(up);
-    const int lane = threadIdx.x;
-    const int64_t i0 = bi * kSbx, j0 = bj * kSby, k0 = bk * kSbz;   // oriented origin
-    // global index of oriented point (ip, jp, kp), all inside the volume
-    auto gidx = [&](int64_t ip, int64_t jp, int64_t kp) {
-        const int64_t i = (dir & 1) ? nx - 1 - ip : ip;
-        const int64_t j = (dir & 2) ? ny - 1 - jp : jp;
-        const int64_t k = (dir & 4) ? nz - 1 - kp : kp;
-        return (k * ny + j) * nx + i;
-    };
-    // all loads issued before any is used (clamped into the volume, so none
-    // sits under a branch), then staged with the absent points set to kFar
-    constexpr int NL = (TX * TY * TZ + 63) / 64;
-    float v[NL];
+    // The point of line (j', k') on hyperplane s has i' = s - j' - k', so its
+    // element index is linear in (s, j', k'): a lane's addresses along the
+    // block are additions.
+    const int sx = (dir & 1) ? -1 : 1;
+    const int64_t dj = ((dir & 2) ? -(int64_t)nx : (int64_t)nx) - sx;
+    const int64_t dk = ((dir & 4) ? -(int64_t)nx * ny : (int64_t)nx * ny) - sx;
+    const int64_t org = ((dir & 4) ? (int64_t)(nz - 1) * nx * ny : 0) +
+                        ((dir & 2) ? (int64_t)(ny - 1) * nx : 0) + ((dir & 1) ? nx - 1 : 0);
+    // Staging: half-wave h takes lines lj = h, h + 8, (h + 16) of each lk, its
+    // lanes the 32 planes of the block, which are consecutive in memory.  All
+    // loads are issued before any is used (an absent point loads element 0,
+    // so none sits under a branch), then staged with those points as kFar.
+    const int h = tid >> 5, tp = tid & 31;
+    constexpr int NJ = 3;
+    float v[T][NJ], ve[3];
+    uint32_t in[T];
 #pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int c = min(lane + 64 * r, TX * TY * TZ - 1);
-        const int lx = c % TX, ly = (c / TX) % TY, lz = c / (TX * TY);
-        const int64_t ip = min(max(i0 - 1 + lx, (int64_t)0), nx - 1);
-        const int64_t jp = min(max(j0 - 1 + ly, (int64_t)0), ny - 1);
-        const int64_t kp = min(max(k0 - 1 + lz, (int64_t)0), nz - 1);
-        v[r] = u[gidx(ip, jp, kp)];
-    }
+    for (int lk = 0; lk < T; ++lk) {
+        const int k = k0 + lk - 1;
+        const bool kok = k >= 0 && k < nz;
+        const int64_t rk = org + (int64_t)k * dk + (int64_t)sx * s0;   // uniform
+        in[lk] = 0;
 #pragma unroll
-    for (int r = 0; r < NL; ++r) {
-        const int c = lane + 64 * r;
-        if (c < TX * TY * TZ) {
-            const int lx = c % TX, ly = (c / TX) % TY, lz = c / (TX * TY);
-            const int64_t ip = i0 - 1 + lx, jp = j0 - 1 + ly, kp = k0 - 1 + lz;
-            const bool in = ip >= 0 && ip < nx && jp >= 0 && jp < ny && kp >= 0 && kp < nz;
-            (&tile[0][0][0])[c] = in ? v[r] : kFar;
+        for (int q = 0; q < NJ; ++q) {
+            const int lj = h + 8 * q, j = j0 + lj - 1, i = s0 + tp - j - k;
+            const bool ok = kok && lj < T && j >= 0 && j < ny && (uint32_t)i < (uint32_t)nx;
+            const int64_t at = rk + j * dj + sx * tp;
+            v[lk][q] = u[ok ? at : 0];
+            in[lk] |= ok ? 1u << q : 0u;
         }
     }
-    __syncwarp();
-    const int ly = 1 + lane % kSby, lz = 1 + lane / kSby;
-    const bool line_in = j0 + ly - 1 < ny && k0 + lz - 1 < nz;
-    for (int s = 0; s < kSbx + kSby + kSbz - 2; ++s) {
-        const int lx = 1 + s - (ly - 1) - (lz - 1);
-        if (line_in && lx >= 1 && lx <= kSbx && i0 + lx - 1 < nx) {
-            const float a = fminf(tile[lz][ly][lx - 1], tile[lz][ly][lx + 1]);
-            const float b = fminf(tile[lz][ly - 1][lx], tile[lz][ly + 1][lx]);
-            const float c = fminf(tile[lz - 1][ly][lx], tile[lz + 1][ly][lx]);
-            if (!(a >= kFar && b >= kFar && c >= kFar)) {
-                const float v = godunov(a, b, c);
-                if (v < tile[lz][ly][lx]) tile[lz][ly][lx] = v;
-            }
-        }
-        __syncwarp();
+    // the planes before and after the block's, for all lines
+    bool ine[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int c = tid + NT * r, t = c < T * T ? -1 : kSs, l = c < T * T ? c : c - T * T;
+        const int j = j0 + l % T - 1, k = k0 + l / T - 1, i = s0 + t - j - k;
+        ine[r] = c < 2 * T * T && j >= 0 && j < ny && k >= 0 && k < nz && (uint32_t)i < (uint32_t)nx;
+        ve[r] = u[ine[r] ? org + (int64_t)k * dk + j * dj + (int64_t)sx * (s0 + t) : 0];
     }
-    for (int c = lane; c < kSbx * kSby * kSbz; c += 64) {
-        const int lx = c % kSbx, ly2 = (c / kSbx) % kSby, lz2 = c / (kSbx * kSby);
-        const int64_t ip = i0 + lx, jp = j0 + ly2, kp = k0 + lz2;
-        if (ip < nx && jp < ny && kp < nz) u[gidx(ip, jp, kp)] = tile[lz2 + 1][ly2 + 1][lx + 1];
+    if (tid == 0) any = 0;
+#pragma unroll
+    for (int lk = 0; lk < T; ++lk)
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) {
+            const float w = in[lk] >> q & 1 ? v[lk][q] : kFar;
+            if (q < 2 || h < T - 16) tile[(tp + 1) * PL + lk * T + h + 8 * q] = w;
+        }
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int c = tid + NT * r, t = c < T * T ? 0 : kSs + 1, l = c < T * T ? c : c - T * T;
+        if (c < 2 * T * T) tile[t * PL + l] = ine[r] ? ve[r] : kFar;
+    }
+    __syncthreads();
+    const int lj = tid % kSj, lk = tid / kSj;
+    // planes on which the thread's line has a point: ta .. ta + tn - 1
+    const int i0 = s0 - (j0 + lj) - (k0 + lk);              // i' at the first plane
+    const bool line_in = j0 + lj < ny && k0 + lk < nz;
+    const int ta = max(0, -i0), tn = line_in ? max(min(kSs, nx - i0) - ta, 0) : 0;
+    float *p = &tile[(lk + 1) * T + lj + 1];                // own line, plane s - 1
+    float prev = p[0], me = p[PL];
+#pragma unroll 2
+    for (int t = 0; t < kSs; ++t, p += PL) {
+        const float next = p[2 * PL];
+        const float bb = min_num(p[-1], p[2 * PL + 1]);
+        const float c = min_num(p[-T], p[2 * PL + T]);
+        float a = min_num(prev, next);
+        const float w = godunov(a, bb, c);   // a: the smallest of the three now
+        if (w < me && (uint32_t)(t - ta) < (uint32_t)tn && !(a >= kFar)) {
+            me = w;
+            p[PL] = w;
+            any = 1;
+        }
+        prev = me;
+        me = next;
+        __syncthreads();
+    }
+    if (!any) return;
+    // planes 1..kSs of the block's own lines
+#pragma unroll 4
+    for (int lk2 = 0; lk2 < kSj; ++lk2) {
+        const int k = k0 + lk2;
+        const int64_t rk = org + (int64_t)k * dk + (int64_t)sx * s0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int lj2 = h + 8 * q, j = j0 + lj2, i = s0 + tp - j - k;
+            if (k < nz && j < ny && (uint32_t)i < (uint32_t)nx)
+                u[rk + j * dj + sx * tp] = tile[(tp + 1) * PL + (lk2 + 1) * T + lj2 + 1];
+        }
     }
 }
 
@@ -488,23 +567,31 @@ hipError_t launch_seeds(const float *doh, const float *tr, const float *maxv, fl
     return hipGetLastError();
 }
 
-int64_t sweep_block_planes(int64_t nx, int64_t ny, int64_t nz)
+int64_t sweep_wavefronts(int64_t nx, int64_t ny, int64_t nz)
 {
-    return (nx + kSbx - 1) / kSbx + (ny + kSby - 1) / kSby + (nz + kSbz - 1) / kSbz - 2;
+    const int64_t nbj = (ny + kSj - 1) / kSj, nbk = (nz + kSj - 1) / kSj;
+    return (nx + ny + nz - 2 + kSs - 1) / kSs + nbj + nbk - 2;
 }
 
-hipError_t launch_sweep_blocks(float *u, int64_t nx, int64_t ny, int64_t nz, int dir, int64_t H,
+hipError_t launch_sweep_blocks(float *u, int64_t nx, int64_t ny, int64_t nz, int dir, int64_t W,
                                hipStream_t s)
 {
-    const int64_t nbx = (nx + kSbx - 1) / kSbx, nby = (ny + kSby - 1) / kSby,
-                  nbz = (nz + kSbz - 1) / kSbz;
-    // bk' runs over the values for which some (bi', bj') completes the plane
-    const int64_t klo = std::max<int64_t>(0, H - (nbx - 1) - (nby - 1));
-    const int64_t khi = std::min<int64_t>(nbz - 1, H);
+    // (hyperplane numbers and block indices are 32 bits wide; every dimension
+    // is at most 2^28, so their sums fit)
+    const int64_t nbj = (ny + kSj - 1) / kSj, nbk = (nz + kSj - 1) / kSj,
+                  nb = (nx + ny + nz - 2 + kSs - 1) / kSs;
+    // block diagonals D = J + K with b = W - D hyperplanes in the volume: the
+    // block's first is s = kSs b, its lines span kSj D .. kSj D + 2 (kSj - 1)
+    // + nx - 1
+    const int64_t dlo = std::max<int64_t>(0, W - (nb - 1));
+    const int64_t dhi = std::min<int64_t>(nbj + nbk - 2, W);
+    if (dhi < dlo) return hipSuccess;
+    const int64_t klo = std::max<int64_t>(0, dlo - (nbj - 1)), khi = std::min<int64_t>(nbk - 1, dhi);
     if (khi < klo) return hipSuccess;
-    const int64_t g = nby * (khi - klo + 1);
-    hipLaunchKernelGGL(sweep_block_kernel, dim3((unsigned)g), dim3(64), 0, s, u, nx, ny, nz, dir,
-                       H, nbx, nby, klo);
+    const int64_t g = nbj * (khi - klo + 1);
+    if (g > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sweep_block_kernel, dim3((unsigned)g), dim3(kSj * kSj), 0, s, u, (int)nx,
+                       (int)ny, (int)nz, dir, (int)W, (int)nb, (int)nbj, (int)klo);
     return hipGetLastError();
 }
 
