@@ -517,12 +517,14 @@ rsf_status make_plan(rsf_context *ctx, Plan &P, const rsf_tile *tiles, int n, in
     P.R2 = P.k2 ? radius_of(p.sigma2) : 0;
     if (P.k2) P.taps2 = make_taps(p.sigma2, P.R2);
     const bool fuse = decide_fuse(ctx, p, probe != nullptr, tiles, n, image);
+    const int halo = rsf::host::xyf_halo(p.force, P.R);
+    const std::vector<Split> splits = splits_for(ctx, tiles, n, P.R, fuse, halo);
     std::vector<Grid3> grids;
     for (int t = 0; t < n; ++t) grids.push_back(grid_of(tiles[t]));
-    const rsf::host::XyfShape f = rsf::host::xyf_shape(grids, p.force, P.R, probe != nullptr);
+    const rsf::host::XyfShape f =
+        rsf::host::xyf_shape(grids, splits, p.force, P.R, probe != nullptr);
     P.shape_f = f;
-    P.L = plan_layout(tiles, n, iters, p.storage, splits_for(ctx, tiles, n, P.R, fuse, f.halo), P.k2,
-                      f.halo, f.nw);
+    P.L = plan_layout(tiles, n, iters, p.storage, splits, P.k2, f.halo, f.nw);
     P.base = base;
     // the table is built on the host: in the pinned staging buffer and
     // copied, or (table_by_kernel) in a kernel argument, allocating nothing
@@ -646,7 +648,7 @@ rsf_status iteration(rsf_context *ctx, const Plan &P, bool probe, hipStream_t s,
                                        paper ? (P.k2 ? rsf::XY_PAPER2 : rsf::XY_PAPER)
                                              : rsf::XY_RSF,
                                        P.image, P.storage, P.f, P.blocks_f, P.shape_f.nw,
-                                       P.shape_f.threads, P.taps, P.c, probe, s);
+                                       P.shape_f.threads, P.shape_f.lds, P.taps, P.c, probe, s);
             }),
             "xy");
     HIP_TRY(timed(ctx, RSF_PASS_Z_UPDATE, s, [&] {

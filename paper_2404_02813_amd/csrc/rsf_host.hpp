@@ -186,19 +186,32 @@ enum PassKind { PASS_XY, PASS_Z, PASS_U, PASS_F };
 // stages in the pass (RSF force), none with one.
 inline int xyf_halo(int force, int R) { return force == RSF_FORCE_PAPER ? 0 : R; }
 
-// The xy pass's workgroups for a batch: most waves of one (probes run with
-// 4), and the threads its widest strip needs.
+// The xy pass's workgroups for a batch of tiles with these splits: most waves
+// of one (probes run with 4) or 2 for the small-volume form, the threads of
+// the widest strip, and the small form's LDS bytes.
 struct XyfShape {
-    int halo, nw, threads;
+    int halo, nw, threads, lds;
 };
-inline XyfShape xyf_shape(const std::vector<Grid3> &g, int force, int R, bool probe)
+inline XyfShape xyf_shape(const std::vector<Grid3> &g, const std::vector<Split> &sp, int force,
+                          int R, bool probe)
 {
-    XyfShape f{xyf_halo(force, R), 4, 64};
-    int least = 0;
-    for (const Grid3 &q : g) least = least == 0 ? q.nx : std::min(least, q.nx);
-    if (!probe && g.size() == 1) f.nw = xyf_pick(g[0], R, f.halo).nw;
-    else if (!probe && !g.empty()) f.nw = xyf_waves(least, f.halo);
-    for (const Grid3 &q : g) f.threads = std::max(f.threads, xyf_threads(q.nx, f.halo, f.nw));
+    XyfShape f{xyf_halo(force, R), 4, 64, 0};
+    if (probe || g.empty()) {
+    } else if (g.size() == 1) {
+        const XyfPick p = xyf_pick(g[0], R, f.halo);
+        f.nw = p.nw == 2 && p.f != sp[0].f ? 4 : p.nw;   // (the form holds only its own chunks)
+    } else {
+        int least = g[0].nx;
+        for (const Grid3 &q : g) least = std::min(least, q.nx);
+        f.nw = xyf_waves(least, f.halo);
+    }
+    if (f.nw == 2) {
+        const int len = (g[0].ny + sp[0].f - 1) / sp[0].f;
+        f.threads = kXysThreads;
+        f.lds = (int)xys_lds(len, R, (xyf_strips(g[0].nx, f.halo, 2).width + 63) / 64);
+    } else {
+        for (const Grid3 &q : g) f.threads = std::max(f.threads, xyf_threads(q.nx, f.halo, f.nw));
+    }
     return f;
 }
 

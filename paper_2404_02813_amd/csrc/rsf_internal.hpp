@@ -192,14 +192,49 @@ inline int64_t resident_f(int R, int nw, int waves)
     const int per_cu = by_regs < by_lds ? by_regs : by_lds;
     return kCus * (int64_t)(per_cu < 1 ? 1 : per_cu);
 }
+// The small-volume form of the xy pass (RSF force): a workgroup of 8 waves
+// holds a chunk's rows in LDS.  Groups of four rows that are x-convolved in
+// stage 1, whose fits are taken, and that are stored, for `len` rows.
+constexpr int kXysThreads = 512;
+struct XysRows {
+    int a, b, c;
+};
+__host__ __device__ inline XysRows xys_rows(int len, int R)
+{
+    XysRows n{};
+    n.c = (len + 3) / 4;
+    n.b = (4 * n.c + 2 * R + 3) / 4;
+    n.a = (4 * n.b + 2 * R + 3) / 4;
+    return n;
+}
+// Row stride (floats) of its rows of 64 nw columns and their halo.
+__host__ __device__ inline int xys_stride(int nw, int R)
+{
+    const int need = 64 * nw + (2 * R + 4 + 3) / 4 * 4;
+    const int m = need % 64;
+    return need + (m <= 16 ? 16 - m : (m <= 48 ? 48 - m : 80 - m));
+}
+inline int64_t xys_lds(int len, int R, int nw)
+{
+    return (int64_t)xys_rows(len, R).a * 4 * 2 * (xys_stride(nw, R) + 64 * nw) * 4;
+}
+constexpr int64_t kXysLds = 156 * 1024;   // of a CU's 160 KB
+
 // Workgroup size (4 or 8 waves) and row chunks of the xy pass for a single
-// volume: the least time of the busiest CU, in rows.  A step of four rows
+// volume, or nw = 2: the small-volume form with f chunks.  For the march: the
+// least time of the busiest CU, in rows.  A step of four rows
 // takes a SIMD about 2600 clocks per resident wave (it is bound by the matrix
 // and vector units) and no less than about 3900 (one wave's own latency), so
 // the time is rounds of resident workgroups x rows (the chunk, `halo` rows of
 // its own and its neighbours' on either side, two groups of latency) x
 // max(1.5, waves per SIMD).  192 x 320 x 352, R = 9, FP16 fields: two strips
-// of 3 waves in two chunks 0.76 x the time of one strip of 6 waves.
+// of 3 waves in two chunks 0.76 x the time of one strip of 6 waves.  The small
+// form's time is that of its products on the busiest CU (each group of four
+// rows of 64 columns 2 (2R + 4) instructions of 8 clocks, 3.6 x that with two
+// waves per SIMD and the rest) plus, per round of resident workgroups, its
+// chain of loads and barriers (about 6 us); 1 us is 3.5 rows in the march's
+// unit.  64^3: 20 -> 12 us; at 108 x 172 x 140, R = 6 it would take 64 us where
+// the march takes 36.
 struct XyfPick {
     int nw, f;
 };
@@ -236,11 +271,11 @@ hipError_t launch_put_table(void *dst, const TableBlob &blob, int bytes, hipStre
 hipError_t launch_xy_one(int R, int image_dtype, int storage_dtype, const Batch &b, int64_t blocks,
                          const Taps &t, const Coeffs &c, hipStream_t s);
 // The iteration's xy pass: P (and K*I, ...) -> Q (mode XY_RSF, XY_PAPER, XY_PAPER2).
-// `nw`: 4 or 8 (xyf_waves); `threads`: 64 times the most waves a strip of
-// the batch's tiles holds.
+// `nw`: 4 or 8 (the march) with `threads`, 64 times the most waves a strip of
+// the batch's tiles holds; or 2 (the small-volume form) with its `lds` bytes.
 hipError_t launch_xyf(int R, int mode, int image_dtype, int storage_dtype, const Batch &b,
-                      int64_t blocks, int nw, int threads, const Taps &t, const Coeffs &c, bool probe,
-                      hipStream_t s);
+                      int64_t blocks, int nw, int threads, int lds, const Taps &t,
+                      const Coeffs &c, bool probe, hipStream_t s);
 // K*I: the z pass of P into KI.
 hipError_t launch_z_plain(int R, int storage_dtype, const Batch &b, int64_t blocks,
                           const Taps &t, int target, hipStream_t s);
@@ -334,8 +369,8 @@ template <int R, class IT, class ST>
 hipError_t launch_xy_one_r(const Batch &b, int64_t blocks, const Taps &t, const Coeffs &c,
                            hipStream_t s);
 template <int R, class IT, class ST>
-hipError_t launch_xyf_r(int mode, const Batch &b, int64_t blocks, int nw, int threads, const Taps &t,
-                        const Coeffs &c, bool probe, hipStream_t s);
+hipError_t launch_xyf_r(int mode, const Batch &b, int64_t blocks, int nw, int threads, int lds,
+                        const Taps &t, const Coeffs &c, bool probe, hipStream_t s);
 template <int R, class ST>
 hipError_t launch_z_plain_r(const Batch &b, int64_t blocks, const Taps &t, int target,
                             hipStream_t s);

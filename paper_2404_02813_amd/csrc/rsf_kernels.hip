@@ -678,10 +678,10 @@ hipError_t launch_xy_one(int R, int it, int st, const Batch &b, int64_t blocks, 
 }
 
 hipError_t launch_xyf(int R, int mode, int it, int st, const Batch &b, int64_t blocks,
-                      int nw, int threads, const Taps &t, const Coeffs &c, bool probe, hipStream_t s)
+                      int nw, int threads, int lds, const Taps &t, const Coeffs &c, bool probe, hipStream_t s)
 {
 #define C(RR, IT, ST) \
-    case RR: return launch_xyf_r<RR, IT, ST>(mode, b, blocks, nw, threads, t, c, probe, s);
+    case RR: return launch_xyf_r<RR, IT, ST>(mode, b, blocks, nw, threads, lds, t, c, probe, s);
     RSF_DISPATCH(C)
 #undef C
 }

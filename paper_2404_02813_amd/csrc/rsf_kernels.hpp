@@ -809,9 +809,15 @@ hipError_t launch_z_plain_r(const Batch &b, int64_t blocks, const Taps &t, int t
 // The iteration's xy pass (mode XY_RSF, XY_PAPER or XY_PAPER2).  Probes run
 // with the smaller workgroups.
 template <int R, class IT, class ST>
-hipError_t launch_xyf_r(int mode, const Batch &b, int64_t blocks, int nw, int threads, const Taps &t,
-                        const Coeffs &c, bool probe, hipStream_t s)
+hipError_t launch_xyf_r(int mode, const Batch &b, int64_t blocks, int nw, int threads, int lds,
+                        const Taps &t, const Coeffs &c, bool probe, hipStream_t s)
 {
+    if (nw == 2) {
+        if (mode != XY_RSF || probe || lds <= 0 || lds > kXysLds) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((xys_kernel<R, ST>), dim3((unsigned)blocks), dim3(kXysThreads), lds, s, b,
+                           t, c);
+        return hipGetLastError();
+    }
     if (threads < 64 || threads > 64 * nw || threads % 64) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block((unsigned)threads);
 #define RSF_XYF(MODE, PROBE, NW) \
@@ -905,7 +911,7 @@ hipError_t launch_z_update_fused_r(const Batch &b, int64_t blocks, const Taps &t
 #define RSF_INSTANTIATE(RR, IT, ST)                                                           \
     template hipError_t launch_xy_one_r<RR, IT, ST>(const Batch &, int64_t, const Taps &,     \
                                                     const Coeffs &, hipStream_t);             \
-    template hipError_t launch_xyf_r<RR, IT, ST>(int, const Batch &, int64_t, int, int,       \
+    template hipError_t launch_xyf_r<RR, IT, ST>(int, const Batch &, int64_t, int, int, int,  \
                                                  const Taps &, const Coeffs &, bool,          \
                                                  hipStream_t);                                \
     template hipError_t launch_z_plain_r<RR, ST>(const Batch &, int64_t, const Taps &, int,   \

@@ -388,8 +388,12 @@ bool launch_chunk(rsf_server *s, std::string &why)
             return p;
         };
         std::vector<Grid3> grids;
-        for (const TileDesc &d : drun) grids.push_back(d.g);
-        const XyfShape shape_f = xyf_shape(grids, gp->req.params.force, gp->R, false);
+        std::vector<Split> splits;
+        for (const TileDesc &d : drun) {
+            grids.push_back(d.g);
+            splits.push_back(d.sp);
+        }
+        const XyfShape shape_f = xyf_shape(grids, splits, gp->req.params.force, gp->R, false);
         std::vector<int> rf(1, 0);
         for (const TileDesc &d : drun) rf.push_back(rf.back() + (int)rsf::xyf_blocks(d.g, d.sp, shape_f.halo,
                                                                                   shape_f.nw));
@@ -521,7 +525,7 @@ bool launch_chunk(rsf_server *s, std::string &why)
                 !ok(rsf::launch_xyf(L.R,
                                     paper ? (L.k2 ? rsf::XY_PAPER2 : rsf::XY_PAPER) : rsf::XY_RSF,
                                     L.image, L.storage, L.run_f.b, L.run_f.blocks, L.shape_f.nw,
-                                    L.shape_f.threads, L.taps, L.c, false, st),
+                                    L.shape_f.threads, L.shape_f.lds, L.taps, L.c, false, st),
                     "xy") ||
                 !ok(L.fuse ? rsf::launch_z_update_fused(L.R, L.image, L.storage, L.run_u.b,
                                                         L.run_u.blocks, L.taps, L.c, paper, st)

@@ -101,6 +101,23 @@ XyfPick xyf_pick(const Grid3 &g, int R, int halo)
             }
         }
     }
+    if (halo == 0) return best;
+    const XyfStrips st = xyf_strips(g.nx, halo, 2);
+    const int waves = (st.width + 63) / 64;
+    for (int c = 1; c <= (g.ny + 3) / 4; ++c) {
+        const int len = (g.ny + c - 1) / c;
+        const int64_t lds = xys_lds(len, R, waves);
+        if ((g.ny + len - 1) / len != c || lds > kXysLds) continue;
+        const XysRows n = xys_rows(len, R);
+        const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
+        const int64_t at_once = std::min(per_cu, std::min<int64_t>(2, kXysLds / lds));
+        const double work = (n.a + 2 * n.b + n.c) * waves * 2.0 * (2 * R + 4) * 8.0 / 4.0 * 3.6 / 2300.0;
+        const double us = (double)((per_cu + at_once - 1) / at_once) * 6.0 + per_cu * work;
+        if (3.5 * us < 0.97 * least) {
+            least = 3.5 * us;
+            best = XyfPick{2, c};
+        }
+    }
     return best;
 }
 

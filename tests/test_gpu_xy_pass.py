@@ -76,3 +76,36 @@ def test_row_chunks_do_not_change_phi(rsf, shape, storage):
             out.append(phi)
     for o in out[1:]:
         assert torch.equal(o, out[0])
+
+
+# LDS of the small-volume form from 43 KB (sigma 1.3, one wave of columns) to
+# 146 KB; one, two and three strips of 128 columns, a last strip of its own
+# width, chunks of 2 to 16 rows, rows off every multiple of four
+SMALL = [((64, 64, 64), 3.0), ((45, 71, 67), 3.0), ((3, 30, 65), 2.9), ((5, 18, 127), 1.3),
+         ((7, 33, 150), 3.0), ((40, 64, 100), 3.9), ((30, 41, 257), 1.6), ((64, 63, 64), 5.3)]
+
+
+TYPES = [("f32", "f32"), ("u16", "f16"), ("u16", "f32"), ("f32", "bf16")]
+
+
+# (mixed types are built for radii of up to 12)
+@pytest.mark.parametrize("shape,sigma,image,storage",
+                         [(*s, *t) for s in SMALL for t in (TYPES if s[1] < 4 else TYPES[:1])])
+def test_small_form_is_the_march_bitwise(rsf, shape, sigma, image, storage):
+    """The small-volume form takes the march's sums in its order.  A split
+    target makes the march run instead."""
+    import torch
+    I, phi0 = fields(shape, 13)
+    if image == "u16":
+        I = np.round(I * 65535.0).astype(np.uint16)
+    p = rsf.make_params(sigma, 1.0, 1.5, 0.001, 1.0, 0.1, 1.0, storage=storage)
+    out = []
+    with rsf.Context(0) as ctx:
+        vol = torch.from_numpy(I).cuda()
+        for waves in (0, 16):
+            ctx.set_split_targets(waves, 0, 0)
+            phi = torch.from_numpy(phi0).cuda()
+            ctx.evolve_ex(vol, phi, p, 3)
+            torch.cuda.synchronize()
+            out.append(phi)
+    assert torch.equal(out[1], out[0])
