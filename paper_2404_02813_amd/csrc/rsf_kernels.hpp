@@ -382,7 +382,9 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
     static_assert(!(FUSE && PROBE), "probes run the passes separately");
     constexpr int TX = kUx, TY = kUy, NT = kUThreads;
     constexpr int PX = TX + 4, PY = TY + 4;
-    constexpr int QX = TX + 2, QY = TY + 2;
+    // the n, V tiles have the phi tile's row stride, so that a point's addresses
+    // in both differ by a constant: 4 to 10 fewer registers
+    constexpr int QX = PX, QY = TY + 2;
     constexpr int QS = QY * QX;
     constexpr int NPHI = 6, NQ = 3;
     constexpr int NLD = (PX * PY + NT - 1) / NT;
@@ -455,11 +457,10 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
 #pragma unroll
             for (int k = 0; k < NLD; ++k) dst[tid + k * NT] = r.v[k];
         };
-        // n and V at phi-tile point (cx, cy) of slice j
-        auto qcalc = [&](int j, int cx, int cy, float &nx_, float &vx_, float &ny_, float &vy_,
+        // n and V of slice j at phi-tile point c (PX + 1 past their tile's point)
+        auto qcalc = [&](int j, int c, float &nx_, float &vx_, float &ny_, float &vy_,
                          float &nz_, float &vz_) {
             const float *p0 = phi_slot(j), *pm = phi_slot(j - 1), *pp = phi_slot(j + 1);
-            const int c = cy * PX + cx;
             const float gx = 0.5f * (p0[c + 1] - p0[c - 1]);
             const float gy = 0.5f * (p0[c + PX] - p0[c - PX]);
             const float gz = 0.5f * (pp[c] - pm[c]);
@@ -471,13 +472,13 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         if (tid < 2 * TX) hq = (tid < TX ? 0 : QY - 1) * QX + (tid % TX) + 1;
         else if (tid < 2 * TX + 2 * TY) {
             const int k = tid - 2 * TX;
-            hq = (k % TY + 1) * QX + (k < TY ? 0 : QX - 1);
+            hq = (k % TY + 1) * QX + (k < TY ? 0 : TX + 1);
         }
         const int own_q = (ty + 1) * QX + tx + 1;
         // n, V of slice j for the own point (z components returned) and halo
         auto q_phase = [&](int j, float &qnz, float &qvz) {
             float qnx, qvx, qny, qvy;
-            qcalc(j, tx + 2, ty + 2, qnx, qvx, qny, qvy, qnz, qvz);
+            qcalc(j, own_q + PX + 1, qnx, qvx, qny, qvy, qnz, qvz);
             float *q = &sq[(j + 2 * NQ) % NQ][0][0];
             q[0 * QS + own_q] = qnx;
             q[1 * QS + own_q] = qvx;
@@ -485,7 +486,7 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
             q[3 * QS + own_q] = qvy;
             if (hq >= 0) {
                 float a0, a1, a2, a3, a4, a5;
-                qcalc(j, hq % QX + 1, hq / QX + 1, a0, a1, a2, a3, a4, a5);
+                qcalc(j, hq + PX + 1, a0, a1, a2, a3, a4, a5);
                 q[0 * QS + hq] = a0;
                 q[1 * QS + hq] = a1;
                 q[2 * QS + hq] = a2;
@@ -497,6 +498,9 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         const float cxy = glb(d.cx)[min(zt.x, g.nx - 1)] * glb(d.cy)[min(zt.y, g.ny - 1)];
         const gptr<const IT> img = glb(static_cast<const IT *>(d.I));
         auto pair_at = [&](int z) { return bld<Vec2<ST>>(rsrc(tp + (int64_t)z * g.sxy), col); };
+        // (a scalar: kept in a vector register it is one more to hold)
+        const float l12 = __builtin_bit_cast(
+            float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ua.l1 - ua.l2)));
         const int z0 = zt.z0;
         // prologue: phi(z0-2..z0+2), then n, V of z0-1, z0, z0+1
 #pragma unroll
@@ -549,6 +553,26 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
                 }
             }
         }
+        // The taps in vector registers: an FMA with a scalar operand takes a
+        // SIMD 4 clocks, one with three vector operands about 2.5.  The R + 1
+        // taps fit beside the rings without a spill for every radius of the
+        // separate update and for the radii below of the fused one.  512^3
+        // u16/FP16, R = 9, fused 785 -> 763 us; u16/BF16, R = 12, separate
+        // 592 -> 571 us; where they do not fit the spills cost far more
+        // (u16/FP16, R = 12, fused 3.21 -> 6.51 ms).
+        constexpr bool kVTaps = !FUSE || (PACK ? R <= 10 : R <= 7);
+        float tv[kVTaps ? R + 1 : 1];
+        if constexpr (kVTaps) {
+#pragma unroll
+            for (int k = 0; k <= R; ++k) {
+                tv[k] = t.w[k];
+                pin(tv[k]);
+            }
+        }
+        auto utap = [&](int k) {
+            if constexpr (kVTaps) return tv[k <= R ? k : 2 * R - k];
+            else return tap<R>(t, k);
+        };
         __builtin_amdgcn_sched_barrier(0);
         // A stage holds the loads of one step: the phi slice, the conv
         // inputs, the image (PAPER: the force field instead) and the z edge
@@ -618,8 +642,8 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
                 float acc_a = 0.f, acc_b = 0.f;
 #pragma unroll
                 for (int k = 0; k < W; ++k) {
-                    acc_a = fmaf(tap<R>(t, k), ha[(s + k) % M], acc_a);
-                    acc_b = fmaf(tap<R>(t, k), hb[(s + k) % M], acc_b);
+                    acc_a = fmaf(utap(k), ha[(s + k) % M], acc_a);
+                    acc_b = fmaf(utap(k), hb[(s + k) % M], acc_b);
                 }
                 // 16-bit storage: opaque sums, so that the compiler cannot
                 // merge the last FMA with the conversion (one rounding to 16
@@ -669,18 +693,18 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
 #pragma unroll
                 for (int k = 0; k < W; ++k) {
                     if constexpr (PACK) {
-                        KG1 = fmaf(tap<R>(t, k), to_f(rv[(s + k) % M].x), KG1);
-                        KG2 = fmaf(tap<R>(t, k), to_f(rv[(s + k) % M].y), KG2);
+                        KG1 = fmaf(utap(k), to_f(rv[(s + k) % M].x), KG1);
+                        KG2 = fmaf(utap(k), to_f(rv[(s + k) % M].y), KG2);
                     } else {
-                        KG1 = fmaf(tap<R>(t, k), ra[(s + k) % M], KG1);
-                        KG2 = fmaf(tap<R>(t, k), rb[(s + k) % M], KG2);
+                        KG1 = fmaf(utap(k), ra[(s + k) % M], KG1);
+                        KG2 = fmaf(utap(k), rb[(s + k) % M], KG2);
                     }
                 }
             }
             if (zt.active) {
                 const int64_t zo = (int64_t)z * g.sxy;
                 const float *p0 = phi_slot(z), *pm = phi_slot(z - 1), *pp = phi_slot(z + 1);
-                const int c = (ty + 2) * PX + tx + 2;
+                const int c = own_q + PX + 1;
                 const float cphi = p0[c];
                 const float lap = p0[c + 1] + p0[c - 1] + p0[c + PX] + p0[c - PX] + pp[c] + pm[c] -
                                   6.f * cphi;
@@ -698,7 +722,7 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
                     Fd = Iv;
                 } else {
                     const float K1 = cxy * cz_cur;
-                    Fd = (ua.l1 - ua.l2) * Iv * Iv * K1 - 2.f * Iv * KG1 + KG2;
+                    Fd = l12 * Iv * Iv * K1 - 2.f * Iv * KG1 + KG2;
                 }
                 const float Rt = lap + divV;
                 const float delta = ua.eps_over_pi * rcp(ua.eps2 + cphi * cphi);
@@ -728,10 +752,13 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         // the steps: a step under a branch ends at a join that copies the
         // stage registers of the skipped path, and that copy waits for every
         // load in flight, prefetches included.  They use fast addressing
-        // where the tile allows it and the registers are there (the fused
-        // RSF update, with two rings, spills with it), away from the volume's
-        // far end: step z loads up to slice z + PF + max(R, 3).
-        constexpr bool kFastAddr = !(FUSE && !PAPER);
+        // where the tile allows it and the registers are there, away from the
+        // volume's far end: step z loads up to slice z + PF + max(R, 3).  The
+        // fused RSF update has them with a packed stage-2 ring (1024^2 x 512,
+        // u16/FP16, R = 12: 3.63 -> 3.21 ms; 512^3, FP16, R = 9: 863 -> 785 us)
+        // and with FP32 rings up to radius 7; beyond that it would spill
+        // (512^3, R = 9: 856 -> 1607 us).
+        constexpr bool kFastAddr = !FUSE || PAPER || PACK || R <= 7;
         constexpr int kAhead = PF + (R > 3 ? R : 3);
         if constexpr (kFastAddr) {
             if (fast) {
