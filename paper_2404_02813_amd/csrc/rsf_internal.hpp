@@ -177,7 +177,8 @@ Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_t
 Split default_split(const Grid3 &g, double share = 1.0, const Targets &tg = kDefaultTargets);
 // Split of a single volume from the resident capacity of the z and update
 // passes (R: Gaussian radius): z chunks are chosen so that the launches' last
-// round of workgroups is not left nearly empty.
+// round of workgroups is not left nearly empty, and down to 2 slices long where
+// the volume is too small to fill the GPU.
 Split capacity_split(const Grid3 &g, int R, int halo);
 // Workgroups the GPU keeps resident at once: z passes (256-thread groups at
 // 8 per CU) and the update pass (512-thread groups at 2 per CU), on 256 CUs.
@@ -242,7 +243,7 @@ XyfPick xyf_pick(const Grid3 &g, int R, int halo);
 // Update-pass workgroups of a tile under any valid split are at most this.
 __host__ __device__ inline int64_t u_blocks_max(const Grid3 &g)
 {
-    return (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy) * ((g.nz + 7) / 8);
+    return (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy) * ((g.nz + 1) / 2);
 }
 bool split_valid(const Grid3 &g, const Split &s);
 

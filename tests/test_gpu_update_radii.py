@@ -42,3 +42,30 @@ def test_fused_update_is_the_separate_passes(image, storage, sigma):
             out.append((phi, ctx.profile_read()["z_heaviside"][0]))
     assert torch.equal(out[0][0], out[1][0])
     assert (out[0][1], out[1][1]) == (4, 1)
+
+
+# chunks of 2 to 4 slices in the update pass and of 2 to 8 in the z pass, with a
+# shorter last one
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(9, 9, 9), (13, 20, 30), (64, 64, 64), (45, 71, 67), (31, 8, 64)])
+def test_short_z_chunks_do_not_change_phi(shape, storage):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2404_02813_amd import rsf
+    rng = np.random.Generator(np.random.PCG64(19))
+    vol = torch.from_numpy(rng.uniform(0.0, 1.0, shape).astype(np.float32)).cuda()
+    phi0 = torch.from_numpy(rng.uniform(-3.0, 3.0, shape).astype(np.float32)).cuda()
+    p = rsf.make_params(3.0, 1.0, 1.5, 0.001, 1.0, 0.1, 1.0, storage=storage)
+    out = []
+    with rsf.Context(0) as ctx:
+        ctx.set_fusion(False)
+        for z, u in ((0, 0), (1, 1)):   # its own chunks; whole in z
+            ctx.set_split_targets(0, z, u)
+            phi = phi0.clone()
+            ctx.evolve_ex(vol, phi, p, 3)
+            torch.cuda.synchronize()
+            out.append((phi, ctx.stats(cap=0)[2]))
+    assert torch.equal(out[0][0], out[1][0])
+    # FP64 sums of the same terms in another order
+    assert out[0][1] == pytest.approx(out[1][1], rel=1e-12)
