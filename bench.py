@@ -25,13 +25,18 @@ METRIC = "Gvoxel-iter/s at 512^3 sigma=3 (% HBM peak); p50/p99 tile latency"
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 
 def pass_bytes(image_bytes: int = 4, storage_bytes: int = 4, paper: bool = False,
-               fused: bool = False) -> dict:
+               fused: bool = False, merged: bool = False) -> dict:
     """Algorithmic HBM bytes per voxel for one launch of each pass: the reads
     and writes the pass must make, each field once (phi is always FP32).
     paper: the Sec. 4.2 force with sigma2 = 0 (no second Gaussian stage; the
     force itself is FP32).  fused: the update also writes the next
-    iteration's stage-1 pair, so z_heaviside runs once per evolution."""
+    iteration's stage-1 pair, so z_heaviside runs once per evolution.
+    merged: one xy pass forms the fits and the force (the form that runs);
+    its bytes are those of xy_fits, and xy_force has none."""
     i, s = image_bytes, storage_bytes
+    if merged:
+        split = pass_bytes(i, s, paper, fused)
+        return {k: v for k, v in split.items() if k != "xy_force"}
     if fused and not paper:
         return {
             "xy_fits": 5 * s,                  # Kz*(HI), Kz*H, K*I -> g1, g2
@@ -62,8 +67,8 @@ def pass_bytes(image_bytes: int = 4, storage_bytes: int = 4, paper: bool = False
 PAPER_CONTEXT = {"ms_per_step": 585.0, "gvoxel_iter_s": 0.214, "volume": "500^3",
                  "hardware": "unstated CUDA GPU", "source": "Table 1 (sum of per-kernel times)"}
 
-PASS_BYTES = pass_bytes()               # FP32 image and fields
-ITER_BYTES = sum(PASS_BYTES.values())   # 72 B per voxel-iteration
+PASS_BYTES = pass_bytes(merged=True)    # FP32 image and fields
+ITER_BYTES = sum(PASS_BYTES.values())   # 56 B per voxel-iteration
 COPY_BYTES = 1 << 30
 
 # name -> (workload, image dtype, storage dtype, force form)
@@ -83,9 +88,10 @@ def workloads():
         big.name + "_u16_f16_paper": (big, "u16", "f16", "paper"),
     }
 
-# the sources that define the four pass kernels (their launch dispatch and
+# the sources that define the pass kernels (their launch dispatch and
 # the set-up, reduction and initialisation kernels live elsewhere)
 KERNEL_SOURCES = ["paper_2404_02813_amd/csrc/rsf_kernels.hpp",
+                  "paper_2404_02813_amd/csrc/rsf_xyf.hpp",
                   "paper_2404_02813_amd/csrc/rsf_device.hpp",
                   "paper_2404_02813_amd/csrc/rsf_internal.hpp"]
 
@@ -114,18 +120,16 @@ def traffic_for(kernel: str, workload: str):
     return rec.get("bytes_per_launch")
 
 
-KERNEL_PASS = (("z_heaviside_kernel<", "z_heaviside"), ("xy_kernel<", None),
-               ("z_update_kernel<", "z_update"))
+KERNEL_PASS = (("z_heaviside_kernel<", "z_heaviside"), ("z_update_kernel<", "z_update"))
 
 
 def _pass_of(kernel_name: str):
     """Map a device kernel name (demangled, or mangled as rocprofv3 leaves
-    FP16 instances) to its pass (xy mode 1 = force, 2 and 3 = fits)."""
+    FP16 instances) to its pass; the xy pass has two forms (xyf_kernel,
+    xys_kernel) and is reported as xy_fits."""
     import re
-    m = re.search(r"xy_kernel<\d+, (\d)", kernel_name) or \
-        re.search(r"xy_kernelILi\d+ELi(\d)E", kernel_name)
-    if m:
-        return {"1": "xy_force", "2": "xy_fits", "3": "xy_fits"}.get(m.group(1))
+    if re.search(r"xy[fs]_kernel(<|ILi)", kernel_name):
+        return "xy_fits"
     m = re.search(r"z_heaviside_kernelILi\d+ELb(\d)E", kernel_name)
     if m:
         return "z_heaviside" if m.group(1) == "0" else None
@@ -273,11 +277,10 @@ def copy_bandwidth(torch) -> float:
 
 
 # Read and write mixes of the passes in 4-byte fields per voxel (FP32 storage):
-# the stage-1 z pass reads phi and I and writes the pair; the fits read the
-# stage-1 pair and K*I and write (g1, g2); the force pass reads and writes one
-# pair; the update reads the stage-2 pair, I and phi and writes phi' (and,
+# the stage-1 z pass reads phi and I and writes the pair; the xy pass reads the
+# stage-1 pair and K*I and writes the stage-2 pair; the update reads the stage-2 pair, I and phi and writes phi' (and,
 # fused, the next stage-1 pair).
-STREAM_MIXES = {"copy": (1, 1), "z_heaviside": (2, 2), "xy_fits": (3, 2), "xy_force": (2, 2),
+STREAM_MIXES = {"copy": (1, 1), "z_heaviside": (2, 2), "xy_fits": (3, 2),
                 "z_update": (4, 1), "z_update_fused": (4, 3)}
 
 
@@ -334,7 +337,7 @@ def run_tiles(args, w) -> int:
         import dataclasses
         w = dataclasses.replace(w, iters=args.iters)
     K, W = max(1, args.steps), max(0, args.warmup)
-    pb = pass_bytes()
+    pb = pass_bytes(merged=True)
     t_gen = time.perf_counter()
     vol_host = w.volume()
     tiles = w.tiles(vol_host)
@@ -413,7 +416,8 @@ def run_tiles(args, w) -> int:
                    "edges": list(w.edges), "halo": w.halo, "sigma": w.sigma, "iters": w.iters,
                    "image": "f32", "storage": "f32", "voxels_with_halo": voxels,
                    "voxels_interior": interior, "parallelism": "single_gpu"},
-        "roofline": roofline(prof, pass_bytes(fused=prof["z_heaviside"][0] < prof["z_update"][0]),
+        "roofline": roofline(prof, pass_bytes(fused=prof["z_heaviside"][0] < prof["z_update"][0],
+                                              merged=True),
                              voxels, w.name),
         "interior_value": round(interior * w.iters * K / elapsed / 1e9, 3),
         "batch_default_split_value": rate(t_default),
@@ -503,7 +507,7 @@ def run_volume(args, w, block: int) -> int:
         "config": {"workload": args.workload, "shape_zyx": list(w.shape), "sigma": w.sigma,
                    "iters": w.iters, "block": block, "curtain": R,
                    "parallelism": "single_gpu"},
-        "roofline": roofline(prof, pass_bytes(4, 4, False), boxed, args.workload),
+        "roofline": roofline(prof, pass_bytes(4, 4, False, merged=True), boxed, args.workload),
         "voxels_with_curtains": boxed,
         "passes_ms_per_launch": {k: round(v[1] / max(v[0], 1), 4) for k, v in prof.items()
                                  if v[0]},
@@ -798,7 +802,7 @@ def run_serve(args, w) -> int:
         "stream_peak_resident": st["peak_resident"],
         "stream_peak_gb": round(st["peak_bytes"] / 2**30, 2),
         "alone_vs_mix_bitwise": f"{same}/{len(kept)}",
-        "hbm_frac_path": round(gvi_sat * sum(pass_bytes(2, 2).values()) / HBM_PEAK_GBS, 4),
+        "hbm_frac_path": round(gvi_sat * sum(pass_bytes(2, 2, merged=True).values()) / HBM_PEAK_GBS, 4),
         "input_gen_s": round(t_gen, 1),
     }
     if not args.no_cpu_baseline:
@@ -872,7 +876,8 @@ def main() -> int:
         w = dataclasses.replace(w, iters=args.iters)
     K, W = max(1, args.steps), max(0, args.warmup)
     paper = force_t == "paper"
-    pb = pass_bytes(2 if image_t == "u16" else 4, 4 if storage_t == "f32" else 2, paper)
+    pb = pass_bytes(2 if image_t == "u16" else 4, 4 if storage_t == "f32" else 2, paper,
+                    merged=True)
 
     t_gen = time.perf_counter()
     if image_t == "u16":
@@ -922,7 +927,8 @@ def main() -> int:
     # the fused update launched the stage-1 pass once per evolution
     fused = prof["z_heaviside"][0] < prof["z_update"][0]
     if fused:
-        pb = pass_bytes(2 if image_t == "u16" else 4, 4 if storage_t == "f32" else 2, paper, True)
+        pb = pass_bytes(2 if image_t == "u16" else 4, 4 if storage_t == "f32" else 2, paper, True,
+                        merged=True)
 
     elapsed = t1 - t0
     vox = w.voxels

@@ -267,7 +267,8 @@ rsf_status rsf_autotune_ex(rsf_context *ctx, const rsf_tile *tiles, int n_tiles,
 /* Workgroup targets of a whole batch (xy waves, z-pass workgroups, update-
  * pass workgroups) from which untuned splits are derived, each tile taking
  * its share of the batch's voxels; 0 keeps the built-in value (16384, 2048,
- * 1024).  rsf_autotune starts its search from these and reports the targets
+ * 1024).  A workgroup of an iteration's xy pass counts as 16 of the waves.
+ * rsf_autotune starts its search from these and reports the targets
  * it chose in chosen[0..2].  Results do not depend on them. */
 rsf_status rsf_set_split_targets(rsf_context *ctx, int64_t xy_waves, int64_t z_blocks,
                                  int64_t u_blocks);
@@ -367,9 +368,9 @@ rsf_status rsf_seeds_ex(rsf_context *ctx, const void *volume, int volume_dtype, 
 /* Fast sweeping (Zhao 2005) in place: u (device floats) holds 0 at the
  * seeds and a large value (1e30) elsewhere; `rounds` repetitions of the
  * eight Gauss-Seidel sweep orderings of the Godunov upwind discretisation of
- * |grad u| = 1 on the unit grid.  Each sweep runs over hyperplanes of
- * 32x8x8 blocks (each block swept in LDS along its own hyperplanes), which
- * gives the same updates as the sequential sweep.  One round reaches
+ * |grad u| = 1 on the unit grid.  Each sweep runs over wavefronts of
+ * blocks of 16 x 16 lines by 32 hyperplanes (skewed along x), which gives
+ * the same updates as the sequential sweep.  One round reaches
  * the discrete solution for a single seed; several seeds can need a second
  * (first-round differences of order 1e-4). */
 rsf_status rsf_fast_sweep(rsf_context *ctx, float *u, int64_t nx, int64_t ny, int64_t nz,
@@ -426,8 +427,9 @@ rsf_status rsf_probe(rsf_context *ctx, const void *volume, int volume_dtype, con
 typedef enum {
     RSF_PASS_SETUP = 0,        /* edge tables of K*1 and K*I, once per call   */
     RSF_PASS_Z_HEAVISIDE = 1,  /* z Gaussian of (H I, H)                      */
-    RSF_PASS_XY_FITS = 2,      /* xy Gaussian + region fits -> g1, g2         */
-    RSF_PASS_XY_FORCE = 3,     /* xy Gaussian of (g1, g2)                     */
+    RSF_PASS_XY_FITS = 2,      /* xy Gaussian, region fits, xy Gaussian of
+                                  (g1, g2): one pass                          */
+    RSF_PASS_XY_FORCE = 3,     /* part of RSF_PASS_XY_FITS; no launches       */
     RSF_PASS_Z_UPDATE = 4,     /* z Gaussian + force, curvature, update       */
     RSF_PASS_REDUCE = 5,       /* FP64 sum |dphi|                             */
     /* initialisation (Sec. 4.3) */

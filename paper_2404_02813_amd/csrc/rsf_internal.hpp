@@ -149,7 +149,8 @@ __host__ __device__ inline int xyf_threads(int nx, int halo, int nw)
     return (xyf_strips(nx, halo, nw).width + 63) / 64 * 64;
 }
 // Most waves of a workgroup (4 or 8) for a batch of several tiles whose
-// narrowest has `nx` columns (a single volume: xyf_pick).  Two stages in the pass recompute a 2R-column halo per strip,
+// narrowest has `nx` columns (a single volume: xyf_pick).  Two stages in the
+// pass recompute a 2R-column halo per strip,
 // so rows longer than 256 go to workgroups of 8 waves (512^3, R = 9: one
 // 512-column strip 0.62 ms, three of 183 columns 0.74 ms); narrower tiles
 // would leave half of such a workgroup's LDS unused (a batch of 114- to
@@ -240,10 +241,14 @@ struct XyfPick {
     int nw, f;
 };
 XyfPick xyf_pick(const Grid3 &g, int R, int halo);
-// Update-pass workgroups of a tile under any valid split are at most this.
+// Update-pass workgroups of a tile under any valid split are at most this:
+// chunks of 8 slices, or, where those are fewer than the GPU holds, of 2.
 __host__ __device__ inline int64_t u_blocks_max(const Grid3 &g)
 {
-    return (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy) * ((g.nz + 1) / 2);
+    const int64_t cols = (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy);
+    const int64_t by8 = cols * ((g.nz + 7) / 8), by2 = cols * ((g.nz + 1) / 2);
+    const int64_t small = by2 < kResidentU ? by2 : kResidentU;
+    return by8 > small ? by8 : small;
 }
 bool split_valid(const Grid3 &g, const Split &s);
 

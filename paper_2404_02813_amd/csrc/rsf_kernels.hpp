@@ -557,8 +557,8 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         // SIMD 4 clocks, one with three vector operands about 2.5.  The R + 1
         // taps fit beside the rings without a spill for every radius of the
         // separate update and for the radii below of the fused one.  512^3
-        // u16/FP16, R = 9, fused 785 -> 763 us; u16/BF16, R = 12, separate
-        // 592 -> 571 us; where they do not fit the spills cost far more
+        // with FP16 fields, R = 9, fused 785 -> 763 us; 256 x 512 x 1024,
+        // u16/BF16, R = 12, separate 592 -> 571 us; where they do not fit the spills cost far more
         // (u16/FP16, R = 12, fused 3.21 -> 6.51 ms).
         constexpr bool kVTaps = !FUSE || (PACK ? R <= 10 : R <= 7);
         float tv[kVTaps ? R + 1 : 1];

@@ -148,7 +148,8 @@ XyfPick xyf_pick(const Grid3 &g, int R, int halo)
         const XysRows n = xys_rows(len, R);
         const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
         const int64_t at_once = std::min(per_cu, std::min<int64_t>(2, kXysLds / lds));
-        const double work = (n.a + 2 * n.b + n.c) * waves * 2.0 * (2 * R + 4) * 8.0 / 4.0 * 3.6 / 2300.0;
+        const double work =
+            (n.a + 2 * n.b + n.c) * waves * 2.0 * (2 * R + 4) * 8.0 / 4.0 * 3.6 / 2300.0;
         const double us = (double)((per_cu + at_once - 1) / at_once) * 6.0 + per_cu * work;
         if (3.5 * us < 0.97 * least) {
             least = 3.5 * us;
@@ -182,8 +183,8 @@ static bool chunks_ok(int n, int c)
 
 bool split_valid(const Grid3 &g, const Split &s)
 {
-    return chunks_ok(g.ny, s.xy) && chunks_ok(g.nz, s.z) && chunks_ok(g.nz, s.u) && chunks_ok(g.ny, s.f) &&
-           u_blocks(g, s) <= u_blocks_max(g);
+    return chunks_ok(g.ny, s.xy) && chunks_ok(g.nz, s.z) && chunks_ok(g.nz, s.u) &&
+           chunks_ok(g.ny, s.f) && u_blocks(g, s) <= u_blocks_max(g);
 }
 
 }  // namespace rsf

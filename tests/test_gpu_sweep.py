@@ -1,5 +1,5 @@
-"""Fast sweeping at the edges of its blocks (16 lines of y, 32 planes of z,
-skewed along x), against the FP64 oracle's sweep of the same seeds."""
+"""Fast sweeping at the edges of its blocks (16 x 16 lines by
+32 hyperplanes), against the FP64 oracle's sweep of the same seeds."""
 import numpy as np
 import pytest
 
@@ -7,8 +7,8 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-# (nz, ny, nx): the smallest volume, the fewest lines along each axis, one block
-# and one line or plane less and more, several blocks with remainders, rows
+# (nz, ny, nx): the smallest volume, the fewest lines along each axis, one block's
+# lines and one less and more, several blocks with remainders, rows
 # shorter than the skew and longer than a wave
 SHAPES = [(3, 3, 3), (3, 3, 70), (3, 40, 3), (70, 3, 3), (31, 15, 9), (32, 16, 16), (33, 17, 65),
           (65, 33, 4), (3, 49, 130), (66, 3, 5)]
