@@ -152,11 +152,15 @@ __host__ __device__ inline int xyf_threads(int nx, int halo, int nw)
 // narrowest has `nx` columns (a single volume: xyf_pick).  Two stages in the
 // pass recompute a 2R-column halo per strip,
 // so rows longer than 256 go to workgroups of 8 waves (512^3, R = 9: one
-// 512-column strip 0.62 ms, three of 183 columns 0.74 ms); narrower tiles
-// would leave half of such a workgroup's LDS unused (a batch of 114- to
-// 274-column tiles: 0.74 ms with 4, 1.33 ms with 8).  One stage has no halo
-// to recompute.
-__host__ __device__ inline int xyf_waves(int nx, int halo) { return halo > 0 && nx > 256 ? 8 : 4; }
+// 512-column strip 0.62 ms, three of 183 columns 0.74 ms) if their strips fill
+// at least 7: narrower ones would leave much of such a workgroup's LDS unused
+// and put two waves on one SIMD and one on the others (a batch of 114- to
+// 274-column tiles: 0.74 ms with 4, 1.33 ms with 8).  One stage has no halo to
+// recompute.
+__host__ __device__ inline int xyf_waves(int nx, int halo)
+{
+    return halo > 0 && nx > 256 && xyf_strips(nx, halo, 8).width > 6 * 64 ? 8 : 4;
+}
 // Workgroups of a tile in the iteration's xy pass.
 __host__ __device__ inline int64_t xyf_blocks(const Grid3 &g, const Split &s, int halo, int nw)
 {

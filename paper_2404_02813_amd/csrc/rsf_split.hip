@@ -129,7 +129,9 @@ XyfPick xyf_pick(const Grid3 &g, int R, int halo)
             if ((g.ny + len - 1) / len != c) continue;
             const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
             const int64_t at_once = std::min(per_cu, slots);
-            const double load = std::max(1.5, 0.25 * (double)(at_once * waves));
+            // (more than four waves load the busiest SIMD as a multiple of four)
+            const int on_simds = waves > 4 ? (waves + 3) / 4 * 4 : waves;
+            const double load = std::max(1.5, 0.25 * (double)(at_once * on_simds));
             const int rows = len + (c == 1 ? 0 : c == 2 ? reach / 2 : reach) + 8;
             const double cost = (double)((per_cu + at_once - 1) / at_once) * rows * load;
             if (least < 0.0 || cost < 0.97 * least) {
