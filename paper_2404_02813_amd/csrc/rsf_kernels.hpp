@@ -573,6 +573,10 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
             if constexpr (kVTaps) return tv[k <= R ? k : 2 * R - k];
             else return tap<R>(t, k);
         };
+        // E = mu R + delta X is rounded once in its product with mu and once in
+        // the sum (true), or with delta first: part of the update's result, per
+        // radius and storage, whatever the code around it becomes.
+        constexpr bool kDeltaLast = PAPER || R <= (PACK ? 6 : 7);
         __builtin_amdgcn_sched_barrier(0);
         // A stage holds the loads of one step: the phi slice, the conv
         // inputs, the image (PAPER: the force field instead) and the z edge
@@ -726,8 +730,14 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
                 }
                 const float Rt = lap + divV;
                 const float delta = ua.eps_over_pi * rcp(ua.eps2 + cphi * cphi);
-                const float E = ua.mu * Rt + delta * (ua.nu * kappa - Fd);
-                const float nxt = cphi + ua.dt * E;
+                // Written out: of the two ways to contract E's sum of two
+                // products the compiler takes one by the size of the unrolled
+                // body, and phi' differs by up to 2.4e-7 between them.
+                const float X = fmaf(ua.nu, kappa, -Fd);
+                float E;
+                if constexpr (kDeltaLast) E = fmaf(delta, X, ua.mu * Rt);
+                else E = fmaf(ua.mu, Rt, delta * X);
+                const float nxt = fmaf(ua.dt, E, cphi);
                 if constexpr (F) bst<float>(r_out, col, nxt, (uint32_t)z * (sxy * 4u));
                 else bst<float>(rsrc(phi_out + zo), col, nxt);
                 acc += fabs((double)nxt - (double)cphi);
