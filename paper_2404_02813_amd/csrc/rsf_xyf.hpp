@@ -58,6 +58,56 @@ struct TapOps {
     }
 };
 
+// The zeros of a pattern stand for taps outside the window.  They add nothing
+// while the element is finite; an Inf or NaN times such a zero is a NaN up to
+// three rows or columns past the window, which ones depending on where the
+// groups of four begin, that is on the split.  So sums that hold a NaN are
+// taken again without the zeros, and a non-finite voxel reaches R voxels under
+// any split, as it does in the one-field pass of K*I.  A wrong value is a NaN
+// that its own output row takes in, so the march looks at the sums it completes
+// last (512^3, R = 9: FP32 fields 670 -> 673 us, FP16 588 -> 599) and runs its
+// chunk once more; the small form looks at each of its sums (64^3: 13.8 -> 13.4).
+//
+// The wave's lanes with a NaN among the values (an instruction for two of them).
+__device__ __forceinline__ uint64_t nan_lanes(const f4 &a, const f4 &b)
+{
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, __builtin_fabsf(a[i])),
+                                          __builtin_fabsf(b[i]));
+    return __builtin_amdgcn_ballot_w64(m != m);
+}
+// Sums a[i] of w[k] src[i si + k sk] in the order of k; field b is `fb` on.
+template <int R>
+__device__ __forceinline__ void conv_exact(const float *src, int si, int sk, int fb, const Taps &t,
+                                           f4 &a, f4 &b)
+{
+    a = b = f4{};
+#pragma clang loop unroll(disable)
+    for (int k = 0; k <= 2 * R; ++k) {
+        const float w = t.w[k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] = fmaf(w, src[i * si + k * sk], a[i]);
+            b[i] = fmaf(w, src[fb + i * si + k * sk], b[i]);
+        }
+    }
+}
+// acc + the taps of pattern P inside the window times v
+template <int R, int P>
+__device__ __forceinline__ void tap4_exact(f4 &acc, float v, const TapOps<R> &tp, const Taps &t)
+{
+    if constexpr (P >= 3 && P <= 2 * R) {
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[P / 16], v, acc, 4, P % 16, 0);
+    } else {
+        static_for<4>([&](auto jc) {
+            constexpr int j = jc, k = P - 3 + j;
+            if constexpr (k >= 0 && k <= 2 * R) acc[j] = fmaf(tap<R>(t, k), v, acc[j]);
+        });
+    }
+}
+
 // Raw buffer of exactly `bytes` (at most 2 GiB): a load at an offset outside
 // it returns 0, a store is dropped.  Rows above or below the slice (offsets
 // that are negative, hence huge, or past its end) are then the zero padding
@@ -91,6 +141,15 @@ __device__ __forceinline__ void bst_at(rsrc_t r, uint32_t off, T v)
     }
 }
 
+// Waves per SIMD the march is compiled for: the most its registers allow with
+// no spill (a bound one higher puts 8 to 24 bytes a lane in scratch).
+template <int R, int MODE, bool PROBE, class ST>
+constexpr int xyf_min_waves =
+    PROBE             ? (R <= 9 ? 3 : 2)
+    : MODE == XY_RSF  ? (R <= 7 ? 4 : R <= 9 ? 3 : 2)
+    : sizeof(ST) == 2 ? (R <= 6 ? 5 : R <= 11 ? 4 : 3)
+                      : (R <= 4 ? 5 : R <= 10 ? 4 : R <= 15 ? 3 : 2);
+
 // A workgroup owns a strip of at most 64 NW columns of one slice (64 per
 // wave) and a chunk of rows, and marches down it four rows per step.  Step G:
 //   - rows of group G (with an R halo in x) are in LDS; each lane x-convolves
@@ -105,8 +164,8 @@ __device__ __forceinline__ void bst_at(rsrc_t r, uint32_t off, T v)
 // Rows of group G + 1 are written to the other LDS buffer and those of G + 2
 // loaded meanwhile; one barrier per step.
 template <int R, int MODE, bool PROBE, int NW, class ST, class IMG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(R <= 9 ? 3 : 2)))
-void xyf_kernel(Batch bt, Taps t, Coeffs c)
+__global__ __launch_bounds__(64 * NW)
+__attribute__((amdgpu_waves_per_eu(xyf_min_waves<R, MODE, PROBE, ST>))) void xyf_kernel(Batch bt, Taps t, Coeffs c)
 {
     constexpr bool TWO = MODE == XY_RSF;
     constexpr int NG = (2 * R + 3) / 4 + 1;          // open output groups
@@ -121,6 +180,7 @@ void xyf_kernel(Batch bt, Taps t, Coeffs c)
                                   : (48 - need % 64 + 64) % 64);
     constexpr int BUF = 2 * 4 * S;                   // [field][row][column]
     __shared__ __attribute__((aligned(16))) float lds[(TWO ? 4 : 2) * BUF];
+    __shared__ int redo;                             // a sum of the workgroup's is NaN
 
     Where wh;
     if (!locate(bt, wh)) return;
@@ -136,6 +196,7 @@ void xyf_kernel(Batch bt, Taps t, Coeffs c)
     const int c0 = min(strip * sg.step, g.nx - sg.width);   // first column of the strip
     const int nw = (sg.width + 63) / 64;             // its waves
     for (int i = threadIdx.x; i < (TWO ? 4 : 2) * BUF; i += (int)blockDim.x) lds[i] = 0.f;
+    if (threadIdx.x == 0) redo = 0;
     __syncthreads();
     // Waves past the strip leave.  Which of the workgroup's waves these are
     // turns with the workgroup, so that no SIMD is left with fewer waves.
@@ -191,7 +252,6 @@ void xyf_kernel(Batch bt, Taps t, Coeffs c)
     // sum.  A chunk that starts the volume skips the groups of zeros above it.
     constexpr int GP = TWO ? 2 * R / 4 : GF, GZ = TWO ? GP : (R + PAD) / 4;
     static_assert(GZ <= GP, "the loop starts at step GP");
-    int G = y0 > 0 ? 0 : GZ;
 
     // element offset of row r of n (clamped to one row outside: on planes of
     // a few very long rows, more would wrap around to valid offsets)
@@ -274,7 +334,7 @@ void xyf_kernel(Batch bt, Taps t, Coeffs c)
     };
     // add the four rows to the open groups (group m of the step in slot
     // (T + m) % NG; group NG - 1 starts here), rows in order
-    auto ysum = [&](auto T, f4 *sa, f4 *sb, const f4 &xa, const f4 &xb) {
+    auto ysum = [&](auto T, auto exact, f4 *sa, f4 *sb, const f4 &xa, const f4 &xb) {
         static_for<4>([&](auto ci) {
             static_for<NG>([&](auto cm) {
                 constexpr int i = ci, m = cm;
@@ -284,10 +344,16 @@ void xyf_kernel(Batch bt, Taps t, Coeffs c)
                     // the first row that reaches the newest group
                     constexpr bool first = m == NG - 1 && (i == 0 || p + 1 >= NK);
                     const f4 zero{};
-                    sa[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[p / 16], xa[i],
-                                                               first ? zero : sa[s], 4, p % 16, 0);
-                    sb[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[p / 16], xb[i],
-                                                               first ? zero : sb[s], 4, p % 16, 0);
+                    if constexpr (exact) {
+                        if constexpr (first) sa[s] = sb[s] = zero;
+                        tap4_exact<R, p>(sa[s], xa[i], tp, t);
+                        tap4_exact<R, p>(sb[s], xb[i], tp, t);
+                    } else {
+                        sa[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(
+                            tp.y[p / 16], xa[i], first ? zero : sa[s], 4, p % 16, 0);
+                        sb[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(
+                            tp.y[p / 16], xb[i], first ? zero : sb[s], 4, p % 16, 0);
+                    }
                 }
             });
         });
@@ -296,137 +362,171 @@ void xyf_kernel(Batch bt, Taps t, Coeffs c)
 #pragma unroll
         for (int m = 0; m < NG; ++m) __asm__ volatile("" : "+v"(sa[m]), "+v"(sb[m]));
     };
+    auto conv = [&](auto T, auto exact, int buf, f4 *sa, f4 *sb) {
+        f4 xa, xb;
+        if constexpr (exact) conv_exact<R>(wr + buf - R, S, 1, 4 * S, t, xa, xb);
+        else xconv(buf, xa, xb);
+        ysum(T, exact, sa, sb, xa, xb);
+    };
 
-    f4 a1[NG], b1[NG], a2[TWO ? NG : 1], b2[TWO ? NG : 1];
-#pragma unroll
-    for (int m = 0; m < NG; ++m) a1[m] = b1[m] = f4{};
-    if constexpr (TWO) {
-#pragma unroll
-        for (int m = 0; m < NG; ++m) a2[m] = b2[m] = f4{};
-    }
     const gptr<float> probe_f1 = glb(d.probe_f1), probe_f2 = glb(d.probe_f2),
                       probe_fd = glb(d.probe_Fd);
-    int cur = 0;                                     // LDS buffer of group G
-    put(fetch(G), cur);
-    Rows nxt = fetch(G + 1);
-
-    Point pt;
-    int oth = BUF;
-    // stage 1 of step G; the fits' inputs are loaded here and used after it
-    auto stage1 = [&](auto T, auto fits) {
-        // opaque, or the compiler would keep every LDS address of both
-        // buffers in a register
-        __asm__ volatile("" : "+s"(cur));
-        oth = BUF - cur;
-        __asm__ volatile("" : "+s"(oth));
-        __syncthreads();
-        put(nxt, oth);
-        if constexpr (fits) pt = point(G);
-        nxt = fetch(G + 2);
-        f4 xa, xb;
-        xconv(cur, xa, xb);
-        ysum(T, a1, b1, xa, xb);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto prime = [&](auto j) {   // (the loop below starts in slot 0)
-        G = j;
-        stage1(ic<((j - GP) % NG + NG) % NG>{}, std::false_type{});
-        cur = oth;
-    };
-    if (y0 > 0) static_for<GP>(prime);
-    else static_for<GP - GZ>([&](auto j) { prime(ic<j + GZ>{}); });
-    G = GP;
-
-    auto step = [&](auto T) -> bool {
-        stage1(T, std::true_type{});
-        const f4 A = a1[T], B = b1[T];
-        const int rb = r0 - R + 4 * G;               // rows of the completed group
-        float u[4], v[4];
+    // One march down the chunk; true if one of its sums is NaN (`exact`: the
+    // sums without the patterns' zeros, one step at a time).
+    auto march = [&](auto exact) -> bool {
+        f4 a1[NG], b1[NG], a2[TWO ? NG : 1], b2[TWO ? NG : 1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            // region fits (Sec. 3 local_intensity)
-            const float K1 = cxz * pt.cy[i];
-            const float A2 = to_f(pt.ki[i]) - A[i];
-            const float B2 = K1 - B[i];
-            const float f1 = A[i] * rcp(B[i]);
-            const float f2 = A2 * rcp(B2);
-            if constexpr (MODE == XY_PAPER) {
-                // F+- = (I - r+-)^2 (Sec. 4.2 expansion, sigma2 = 0)
-                const float im = to_f(pt.im[i]);
-                float r1 = f1, r2 = f2;
-                if constexpr (std::is_same<IMG, uint16_t>::value) {
-                    // rounded fits, so that the image's scaling is the product
-                    // that contracts with the difference
-                    pin(r1);
-                    pin(r2);
-                }
-                const float d1 = im - r1, d2 = im - r2;
-                u[i] = c.l1 * d1 * d1 - c.l2 * d2 * d2;
-            } else if constexpr (MODE == XY_PAPER2) {
-                // F+- = K2*I^2 - 2 r+- K2*I + r+-^2 (Sec. 4.2 expansion)
-                const float a = to_f(pt.k2i[i]), q = to_f(pt.k2q[i]);
-                const float F1 = q - 2.f * f1 * a + f1 * f1;
-                const float F2 = q - 2.f * f2 * a + f2 * f2;
-                u[i] = c.l1 * F1 - c.l2 * F2;
-            } else {
-                // inputs of the force convolution; zero outside the volume
-                // (the row's mask opaque: a select would go through VCC)
-                int rk = ~(((rb + i) | (g.ny - 1 - rb - i)) >> 31);
-                __asm__ volatile("" : "+s"(rk));
-                const int keep = xkeep & rk;
-                float g1 = c.l1 * f1 - c.l2 * f2, g2 = c.l1 * f1 * f1 - c.l2 * f2 * f2;
-                if constexpr (!std::is_same<ST, float>::value) {
-                    // rounded to FP32, then to the storage type (opaque: not
-                    // in one step), as every field of an iteration is
-                    pin(g1);
-                    pin(g2);
-                    g1 = to_f(from_f<ST>(g1));
-                    g2 = to_f(from_f<ST>(g2));
-                }
-                u[i] = __int_as_float(__float_as_int(g1) & keep);
-                v[i] = __int_as_float(__float_as_int(g2) & keep);
-            }
-            if constexpr (PROBE) {
-                if (rb + i >= y0 && rb + i < y1 && x >= o0 && x < o1) {
-                    const int64_t at = zb + (int64_t)(rb + i) * g.nx + x;
-                    if (probe_f1) probe_f1[at] = f1;
-                    if (probe_f2) probe_f2[at] = f2;
-                    if (!TWO && probe_fd) probe_fd[at] = u[i];
-                }
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int m = 0; m < NG; ++m) a1[m] = b1[m] = f4{};
         if constexpr (TWO) {
-            // this step's g into the other buffer; the previous step's is
-            // convolved
-            float *const wg = wr + 2 * BUF + oth;
+#pragma unroll
+            for (int m = 0; m < NG; ++m) a2[m] = b2[m] = f4{};
+        }
+        uint64_t nans = 0;
+        int G = y0 > 0 ? 0 : GZ;
+        int cur = 0;                                     // LDS buffer of group G
+        put(fetch(G), cur);
+        Rows nxt = fetch(G + 1);
+
+        Point pt;
+        int oth = BUF;
+        // stage 1 of step G; the fits' inputs are loaded here and used after it
+        auto stage1 = [&](auto T, auto fits) {
+            // opaque, or the compiler would keep every LDS address of both
+            // buffers in a register
+            __asm__ volatile("" : "+s"(cur));
+            oth = BUF - cur;
+            __asm__ volatile("" : "+s"(oth));
+            __syncthreads();
+            put(nxt, oth);
+            if constexpr (fits) pt = point(G);
+            nxt = fetch(G + 2);
+            conv(T, exact, cur, a1, b1);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto step = [&](auto T) -> bool {
+            stage1(T, std::true_type{});
+            const f4 A = a1[T], B = b1[T];
+            const int rb = r0 - R + 4 * G;               // rows of the completed group
+            float u[4], v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                wg[i * S] = u[i];
-                wg[(4 + i) * S] = v[i];
+                // region fits (Sec. 3 local_intensity)
+                const float K1 = cxz * pt.cy[i];
+                const float A2 = to_f(pt.ki[i]) - A[i];
+                const float B2 = K1 - B[i];
+                const float f1 = A[i] * rcp(B[i]);
+                const float f2 = A2 * rcp(B2);
+                if constexpr (MODE == XY_PAPER) {
+                    // F+- = (I - r+-)^2 (Sec. 4.2 expansion, sigma2 = 0)
+                    const float im = to_f(pt.im[i]);
+                    float r1 = f1, r2 = f2;
+                    if constexpr (std::is_same<IMG, uint16_t>::value) {
+                        // rounded fits, so that the image's scaling is the product
+                        // that contracts with the difference
+                        pin(r1);
+                        pin(r2);
+                    }
+                    const float d1 = im - r1, d2 = im - r2;
+                    u[i] = c.l1 * d1 * d1 - c.l2 * d2 * d2;
+                } else if constexpr (MODE == XY_PAPER2) {
+                    // F+- = K2*I^2 - 2 r+- K2*I + r+-^2 (Sec. 4.2 expansion)
+                    const float a = to_f(pt.k2i[i]), q = to_f(pt.k2q[i]);
+                    const float F1 = q - 2.f * f1 * a + f1 * f1;
+                    const float F2 = q - 2.f * f2 * a + f2 * f2;
+                    u[i] = c.l1 * F1 - c.l2 * F2;
+                } else {
+                    // inputs of the force convolution; zero outside the volume
+                    // (the row's mask opaque: a select would go through VCC)
+                    int rk = ~(((rb + i) | (g.ny - 1 - rb - i)) >> 31);
+                    __asm__ volatile("" : "+s"(rk));
+                    const int keep = xkeep & rk;
+                    float g1 = c.l1 * f1 - c.l2 * f2, g2 = c.l1 * f1 * f1 - c.l2 * f2 * f2;
+                    if constexpr (!std::is_same<ST, float>::value) {
+                        // rounded to FP32, then to the storage type (opaque: not
+                        // in one step), as every field of an iteration is
+                        pin(g1);
+                        pin(g2);
+                        g1 = to_f(from_f<ST>(g1));
+                        g2 = to_f(from_f<ST>(g2));
+                    }
+                    u[i] = __int_as_float(__float_as_int(g1) & keep);
+                    v[i] = __int_as_float(__float_as_int(g2) & keep);
+                }
+                if constexpr (PROBE) {
+                    if (rb + i >= y0 && rb + i < y1 && x >= o0 && x < o1) {
+                        const int64_t at = zb + (int64_t)(rb + i) * g.nx + x;
+                        if (probe_f1) probe_f1[at] = f1;
+                        if (probe_f2) probe_f2[at] = f2;
+                        if (!TWO && probe_fd) probe_fd[at] = u[i];
+                    }
+                }
             }
-            f4 ga, gb;
-            xconv(2 * BUF + cur, ga, gb);
-            ysum(T, a2, b2, ga, gb);
-        }
-        const int orow = TWO ? rb - R - 4 - y0 : rb - y0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t off = ((e0 + at_row(orow + i, y1 - y0)) * OB) | obad;
+            __builtin_amdgcn_sched_barrier(0);
             if constexpr (TWO) {
-                Vec2<ST> w;
-                w.x = from_f<ST>(a2[T][i]);
-                w.y = from_f<ST>(b2[T][i]);
-                bst_at<Vec2<ST>>(rout, off, w);
-            } else {
-                bst_at<float>(rout, off, u[i]);
+                // this step's g into the other buffer; the previous step's is
+                // convolved
+                float *const wg = wr + 2 * BUF + oth;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    wg[i * S] = u[i];
+                    wg[(4 + i) * S] = v[i];
+                }
+                conv(T, exact, 2 * BUF + cur, a2, b2);
+                if constexpr (!exact) nans |= nan_lanes(a2[T], b2[T]);
+            } else if constexpr (!exact) {
+                nans |= nan_lanes(A, B);
             }
+            const int orow = TWO ? rb - R - 4 - y0 : rb - y0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t off = ((e0 + at_row(orow + i, y1 - y0)) * OB) | obad;
+                if constexpr (TWO) {
+                    Vec2<ST> w;
+                    w.x = from_f<ST>(a2[T][i]);
+                    w.y = from_f<ST>(b2[T][i]);
+                    bst_at<Vec2<ST>>(rout, off, w);
+                } else {
+                    bst_at<float>(rout, off, u[i]);
+                }
+            }
+            cur = oth;
+            return ++G < gend;
+        };
+        if constexpr (exact) {
+            // (steps before GP too: what they complete is not stored)
+            while (step(ic<0>{})) {
+#pragma unroll
+                for (int m = 0; m + 1 < NG; ++m) {
+                    a1[m] = a1[m + 1];
+                    b1[m] = b1[m + 1];
+                    if constexpr (TWO) {
+                        a2[m] = a2[m + 1];
+                        b2[m] = b2[m + 1];
+                    }
+                }
+            }
+            return false;
+        } else {
+            auto prime = [&](auto j) {   // (the loop below starts in slot 0)
+                G = j;
+                stage1(ic<((j - GP) % NG + NG) % NG>{}, std::false_type{});
+                cur = oth;
+            };
+            if (y0 > 0) static_for<GP>(prime);
+            else static_for<GP - GZ>([&](auto j) { prime(ic<j + GZ>{}); });
+            G = GP;
+            while (all_of_impl(step, std::make_integer_sequence<int, NG>{})) {
+            }
+            return nans != 0;
         }
-        cur = oth;
-        return ++G < gend;
     };
-    while (all_of_impl(step, std::make_integer_sequence<int, NG>{})) {
-    }
+    if (march(std::false_type{})) redo = 1;
+    __syncthreads();
+    if (__builtin_expect(!redo, 1)) return;
+    // (the waves that are left cover the strip: 64 nw threads)
+    for (int i = (int)(wr - lds) - R; i < (TWO ? 4 : 2) * BUF; i += 64 * nw) lds[i] = 0.f;
+    __syncthreads();
+    march(std::true_type{});
 }
 
 // The xy pass of a small volume (RSF force): instead of marching down the
@@ -529,6 +629,8 @@ __global__ __launch_bounds__(kXysThreads, 4) void xys_kernel(Batch bt, Taps t, C
                     }
                 });
             });
+            if (__builtin_expect(nan_lanes(a, b) != 0, 0))
+                conv_exact<R>(A + 4 * gr * S + 64 * w + lane, S, 1, FA, t, a, b);
             float *const dst = B + 4 * gr * BS + 64 * w + lane;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -547,6 +649,7 @@ __global__ __launch_bounds__(kXysThreads, 4) void xys_kernel(Batch bt, Taps t, C
             a = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[p / 16], src[k * BS], a, 4, p % 16, 0);
             b = __builtin_amdgcn_mfma_f32_4x4x1f32(tp.y[p / 16], src[FB + k * BS], b, 4, p % 16, 0);
         });
+        if (__builtin_expect(nan_lanes(a, b) != 0, 0)) conv_exact<R>(src, BS, BS, FB, t, a, b);
     };
 
     xpass(n.a);
