@@ -229,12 +229,14 @@ rsf_status rsf_evolve_batch(rsf_context *ctx, const rsf_tile *tiles, int n_tiles
  * their phi; the caller's buffers are not modified) for candidate workgroup
  * splits of each pass (row chunks of the xy passes, z chunks of the z and
  * update passes), one pass at a time with the passes separate, and keeps the
- * fastest split per tile shape and radius in the context.  Then, where the
- * force and radius allow the fused update (rsf_set_fusion), it times that
- * schedule against the separate passes and keeps the faster for this set of
- * tile shapes.  Later evolutions of the same shapes use both.
- *   chosen : NULL or int64_t[4]: the xy, z and update workgroup targets, and
- *            1 if the fused update was chosen (else 0).
+ * fastest split per tile shape, radius and force in the context, or none where
+ * the untuned split is at least as fast.  Then, where the force and radius
+ * allow the fused update (rsf_set_fusion), it times that schedule against the
+ * separate passes and keeps the faster for this set of tile shapes.  Later
+ * evolutions of the same shapes use both.
+ *   chosen : NULL or int64_t[4]: the xy, z and update workgroup targets (the
+ *            context's own where the untuned split stays), and 1 if the fused
+ *            update was chosen (else 0).
  * phi after an evolution is bitwise independent of the split and schedule;
  * the FP64 sums of |dphi| are grouped per update workgroup, so they may
  * differ in the last bits.  Synchronises `stream`; allocates a scratch copy

@@ -179,7 +179,7 @@ struct rsf_context {
     std::vector<hipEvent_t> ev_pool;
     size_t ev_used = 0;
     std::vector<Rec> recs;
-    // autotuned splits by tile shape and radius
+    // autotuned splits by tile shape, radius and the xy pass's halo (tuned_key)
     std::map<std::vector<int64_t>, Split> tuned;
     // autotuned schedule (fused update or separate passes) by batch: the
     // sorted tile shapes, radius, force, image and storage types
@@ -441,6 +441,13 @@ bool fusable(const rsf_context *ctx, const rsf_params &p, bool probe, int image)
             radius_of(p.sigma) <= rsf::fuse_max_r(p.storage, image));
 }
 
+// Key of a tile's tuned split.  The halo is the force: the row chunks of the xy
+// pass depend on it (one or two Gaussian stages).
+std::vector<int64_t> tuned_key(const rsf_tile &t, int R, int halo)
+{
+    return {t.nx, t.ny, t.nz, R, halo};
+}
+
 std::vector<Split> splits_for(rsf_context *ctx, const rsf_tile *tiles, int n, int R,
                               bool whole_z = false, int halo = 0);
 
@@ -459,7 +466,8 @@ bool decide_fuse(const rsf_context *ctx, const rsf_params &p, bool probe, const 
     const int R = radius_of(p.sigma);
     bool whole = true;
     int64_t cols = 0;
-    const std::vector<Split> sps = splits_for(const_cast<rsf_context *>(ctx), tiles, n, R, false);
+    const std::vector<Split> sps = splits_for(const_cast<rsf_context *>(ctx), tiles, n, R, false,
+                                              rsf::host::xyf_halo(p.force, R));
     for (int t = 0; t < n; ++t) {
         whole = whole && sps[t].u == 1;
         cols += (int64_t)((tiles[t].nx + rsf::kUx - 1) / rsf::kUx) *
@@ -491,7 +499,7 @@ std::vector<Split> splits_for(rsf_context *ctx, const rsf_tile *tiles, int n, in
         const Grid3 g = grid_of(tiles[t]);
         Split s = base_split(ctx, g, sh[t], n, R, halo);
         if (ctx) {
-            auto it = ctx->tuned.find({g.nx, g.ny, g.nz, R});
+            auto it = ctx->tuned.find(tuned_key(tiles[t], R, halo));
             if (it != ctx->tuned.end() && rsf::split_valid(g, it->second)) s = it->second;
         }
         if (whole_z) s.u = 1;
@@ -1306,13 +1314,17 @@ rsf_status rsf_autotune_ex(rsf_context *ctx, const rsf_tile *tiles, int n_tiles,
         int64_t best[3] = {ctx->targets.xy, ctx->targets.z, ctx->targets.u};
         // targets are for the whole batch; each tile gets its voxel share
         const std::vector<double> sh = shares_of(tiles, n_tiles);
+        const int halo = rsf::host::xyf_halo(params->force, R);
+        auto untune = [&] {
+            for (int t = 0; t < n_tiles; ++t) ctx->tuned.erase(tuned_key(tiles[t], R, halo));
+        };
         auto apply = [&](const int64_t tg[3]) {
             for (int t = 0; t < n_tiles; ++t) {
                 const Grid3 g = grid_of(tiles[t]);
                 const auto part = [&](int64_t v) {
                     return (int64_t)std::max(1.0, std::ceil((double)v * sh[t]));
                 };
-                ctx->tuned[{g.nx, g.ny, g.nz, R}] =
+                ctx->tuned[tuned_key(tiles[t], R, halo)] =
                     rsf::make_split(g, part(tg[0]), part(tg[1]), part(tg[2]));
             }
         };
@@ -1347,7 +1359,11 @@ rsf_status rsf_autotune_ex(rsf_context *ctx, const rsf_tile *tiles, int n_tiles,
         // The splits are searched with the passes separate (all three
         // targets then matter); then the schedule: the update fused with
         // the next stage-1 pass (each tile one update chunk) against the
-        // separate passes, where the force and radius allow fusing.
+        // separate passes, where the force and radius allow fusing.  The
+        // untuned splits are timed beside the candidates and stay unless one
+        // is faster: those of a single volume (its own chunks, the small form
+        // of the xy pass) are not among what targets can give (64^3: 33 us an
+        // iteration untuned, 54 with the best targets).
         const std::vector<int64_t> skey = schedule_key(tiles, n_tiles, *params, volume_dtype);
         ctx->tuned_fuse.erase(skey);
         const bool can_fuse = fusable(ctx, *params, false, volume_dtype);
@@ -1372,31 +1388,36 @@ rsf_status rsf_autotune_ex(rsf_context *ctx, const rsf_tile *tiles, int n_tiles,
             if (st != RSF_OK) break;
             best[axis] = keep;
         }
-        int fused_choice = 0;
-        if (st == RSF_OK) {
-            apply(best);
-            if (can_fuse) {
-                float sep = 0.f, fus = 0.f;
-                st = trial(sep);
-                ctx->force_schedule = 1;
-                if (st == RSF_OK) st = trial(fus);
-                if (st == RSF_OK) {
-                    fused_choice = fus < sep ? 1 : 0;
-                    ctx->tuned_fuse[skey] = fused_choice == 1;
+        // the least of two trials of each choice, the choices in turn
+        int fused_choice = 0, candidate = 0;
+        float least = -1.f;
+        for (int turn = 0; turn < 2; ++turn)
+            for (int fus = 0; fus < (can_fuse ? 2 : 1); ++fus)
+                for (int cand = 0; cand < 2 && st == RSF_OK; ++cand) {
+                    if (cand) apply(best);
+                    else untune();
+                    ctx->force_schedule = fus;
+                    float ms = 0.f;
+                    st = trial(ms);
+                    if (st == RSF_OK && (least < 0.f || ms < least)) {
+                        least = ms;
+                        fused_choice = fus;
+                        candidate = cand;
+                    }
                 }
-            }
-        }
         ctx->force_schedule = -1;
         if (st == RSF_OK) {
+            if (candidate) apply(best);
+            else untune();
+            if (can_fuse) ctx->tuned_fuse[skey] = fused_choice == 1;
             if (chosen) {
-                chosen[0] = best[0];
-                chosen[1] = best[1];
-                chosen[2] = best[2];
+                chosen[0] = candidate ? best[0] : ctx->targets.xy;
+                chosen[1] = candidate ? best[1] : ctx->targets.z;
+                chosen[2] = candidate ? best[2] : ctx->targets.u;
                 chosen[3] = fused_choice;
             }
         } else {
-            for (int t = 0; t < n_tiles; ++t)
-                ctx->tuned.erase({tiles[t].nx, tiles[t].ny, tiles[t].nz, R});
+            untune();
         }
         (void)hipStreamSynchronize(s);
         release();
