@@ -195,9 +195,6 @@ __attribute__((amdgpu_waves_per_eu(xyf_min_waves<R, MODE, PROBE, ST>))) void xyf
     constexpr int H = TWO ? R : 0;                   // columns a strip shares with the next
     const int c0 = min(strip * sg.step, g.nx - sg.width);   // first column of the strip
     const int nw = (sg.width + 63) / 64;             // its waves
-    for (int i = threadIdx.x; i < (TWO ? 4 : 2) * BUF; i += (int)blockDim.x) lds[i] = 0.f;
-    if (threadIdx.x == 0) redo = 0;
-    __syncthreads();
     // Waves past the strip leave.  Which of the workgroup's waves these are
     // turns with the workgroup, so that no SIMD is left with fewer waves.
     const int waves = (int)blockDim.x / 64;
@@ -384,8 +381,15 @@ __attribute__((amdgpu_waves_per_eu(xyf_min_waves<R, MODE, PROBE, ST>))) void xyf
         uint64_t nans = 0;
         int G = y0 > 0 ? 0 : GZ;
         int cur = 0;                                     // LDS buffer of group G
-        put(fetch(G), cur);
+        // the first rows are on their way while the LDS is cleared (by the 64 nw
+        // threads that are left)
+        const Rows first = fetch(G);
         Rows nxt = fetch(G + 1);
+        for (int i = 4 * ((int)(wr - lds) - R); i < (TWO ? 4 : 2) * BUF; i += 256 * nw)
+            *reinterpret_cast<f4 *>(lds + i) = f4{};
+        if constexpr (!exact) redo = 0;
+        __syncthreads();
+        put(first, cur);
 
         Point pt;
         int oth = BUF;
@@ -523,9 +527,6 @@ __attribute__((amdgpu_waves_per_eu(xyf_min_waves<R, MODE, PROBE, ST>))) void xyf
     if (march(std::false_type{})) redo = 1;
     __syncthreads();
     if (__builtin_expect(!redo, 1)) return;
-    // (the waves that are left cover the strip: 64 nw threads)
-    for (int i = (int)(wr - lds) - R; i < (TWO ? 4 : 2) * BUF; i += 64 * nw) lds[i] = 0.f;
-    __syncthreads();
     march(std::true_type{});
 }
 
