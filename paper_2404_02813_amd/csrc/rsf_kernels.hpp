@@ -558,13 +558,15 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         // taps fit beside the rings without a spill for the radii below of the
         // fused update and in the separate one, but for R = 10 with FP32 rings,
         // two prefetch stages and a uint16 image (12 bytes a lane); probes need
-        // the registers for their outputs.  512^3 with FP16 fields, R = 9,
+        // the registers for their outputs, and the separate update of the Sec.
+        // 4.2 force has no sums (192 x 320 x 352, FP16: 89 us with its taps
+        // loaded all the same, 86 without).  512^3 with FP16 fields, R = 9,
         // fused 785 -> 763 us; 256 x 512 x 1024, u16/BF16, R = 12, separate
         // 592 -> 571 us; where they do not fit the spills cost far more
         // (u16/FP16, R = 12, fused 3.21 -> 6.51 ms).
         constexpr bool kVTaps =
             !PROBE && (FUSE ? (PACK ? R <= 10 : R <= 7)
-                            : !(R == 10 && std::is_same<ST, float>::value &&
+                            : !PAPER && !(R == 10 && std::is_same<ST, float>::value &&
                                 std::is_same<IT, uint16_t>::value));
         float tv[kVTaps ? R + 1 : 1];
         if constexpr (kVTaps) {
