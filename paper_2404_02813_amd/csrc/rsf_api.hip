@@ -487,7 +487,7 @@ Split base_split(const rsf_context *ctx, const Grid3 &g, double share, int n, in
     const bool own_targets = tg.xy != rsf::kDefaultTargets.xy ||
                              tg.z != rsf::kDefaultTargets.z || tg.u != rsf::kDefaultTargets.u;
     return n == 1 && !own_targets && R > 0 ? rsf::capacity_split(g, R, halo)
-                                           : rsf::default_split(g, share, tg);
+                                           : rsf::default_split(g, share, tg, R, halo);
 }
 
 std::vector<Split> splits_for(rsf_context *ctx, const rsf_tile *tiles, int n, int R,
@@ -889,7 +889,8 @@ size_t autotune_trial_ws(rsf_context *ctx, const rsf_tile *tiles, int n, const r
                         return (int64_t)std::max(1.0, std::ceil((double)v * sh[t]));
                     };
                     // a candidate the tile cannot take leaves it on its base split
-                    const Split c1 = rsf::make_split(g, part(a), part(b), part(c));
+                    const Split c1 = rsf::make_split(g, part(a), part(b), part(c), R,
+                                                     rsf::host::xyf_halo(p.force, R));
                     sp[(size_t)t] = rsf::split_valid(g, c1) ? c1 : base_split(ctx, g, sh[t], n, R);
                 }
                 most = std::max(most, plan_layout(tiles, n, trial_iters + 1, p.storage, sp,
@@ -1325,7 +1326,7 @@ rsf_status rsf_autotune_ex(rsf_context *ctx, const rsf_tile *tiles, int n_tiles,
                     return (int64_t)std::max(1.0, std::ceil((double)v * sh[t]));
                 };
                 ctx->tuned[tuned_key(tiles[t], R, halo)] =
-                    rsf::make_split(g, part(tg[0]), part(tg[1]), part(tg[2]));
+                    rsf::make_split(g, part(tg[0]), part(tg[1]), part(tg[2]), R, halo);
             }
         };
         // time what rsf_evolve_batch would run under the current splits and

@@ -201,9 +201,7 @@ inline XyfShape xyf_shape(const std::vector<Grid3> &g, const std::vector<Split> 
         const XyfPick p = xyf_pick(g[0], R, f.halo);
         f.nw = p.nw == 2 && p.f != sp[0].f ? 4 : p.nw;   // (the form holds only its own chunks)
     } else {
-        int least = g[0].nx;
-        for (const Grid3 &q : g) least = std::min(least, q.nx);
-        f.nw = xyf_waves(least, f.halo);
+        f.nw = xyf_batch_waves(g.data(), sp.data(), (int)g.size(), R, f.halo);
     }
     if (f.nw == 2) {
         const int len = (g[0].ny + sp[0].f - 1) / sp[0].f;

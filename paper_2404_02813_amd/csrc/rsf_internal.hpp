@@ -113,12 +113,11 @@ __host__ __device__ inline int64_t u_blocks(const Grid3 &g, const Split &s)
 }
 
 // Strips of the iteration's xy pass: a workgroup of up to `nw` waves (64
-// columns each) computes the `width` columns from xyf_first and stores all
-// but the `halo` columns it shares with a neighbouring strip.  Of the few
-// smallest strip counts, the one with the fewest waves in all.  With more
-// than one strip every strip is at least 128 wide, so that its threads can
-// load a group's x halo (8 R elements) at one each; the last one is moved
-// left to its full width.
+// columns each) computes `width` columns and stores all but the `halo` columns
+// it shares with a neighbouring strip.  Of the few smallest strip counts, the
+// one with the fewest waves in all.  With more than one strip (4 or 8 waves)
+// every strip is at least 128 wide, so that its threads can load a group's x
+// halo (8 R elements) at one each; the last one is moved left to its full width.
 struct XyfStrips {
     int n, width, step;
 };
@@ -148,19 +147,6 @@ __host__ __device__ inline int xyf_threads(int nx, int halo, int nw)
 {
     return (xyf_strips(nx, halo, nw).width + 63) / 64 * 64;
 }
-// Most waves of a workgroup (4 or 8) for a batch of several tiles whose
-// narrowest has `nx` columns (a single volume: xyf_pick).  Two stages in the
-// pass recompute a 2R-column halo per strip,
-// so rows longer than 256 go to workgroups of 8 waves (512^3, R = 9: one
-// 512-column strip 0.62 ms, three of 183 columns 0.74 ms) if their strips fill
-// at least 7: narrower ones would leave much of such a workgroup's LDS unused
-// and put two waves on one SIMD and one on the others (a batch of 114- to
-// 274-column tiles: 0.74 ms with 4, 1.33 ms with 8).  One stage has no halo to
-// recompute.
-__host__ __device__ inline int xyf_waves(int nx, int halo)
-{
-    return halo > 0 && nx > 256 && xyf_strips(nx, halo, 8).width > 6 * 64 ? 8 : 4;
-}
 // Workgroups of a tile in the iteration's xy pass.
 __host__ __device__ inline int64_t xyf_blocks(const Grid3 &g, const Split &s, int halo, int nw)
 {
@@ -176,10 +162,13 @@ constexpr Targets kDefaultTargets{16384, 2048, 1024};
 
 // Split of one volume aiming at the given workgroup counts per pass (the
 // autotuner varies them); every chunk is non-empty and at least 8 long.
-Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_target);
+// R, halo: Gaussian radius and halo of the iteration's xy pass.
+Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_target, int R = 9,
+                 int halo = 9);
 // Split of a tile holding fraction `share` of its batch's voxels: that share
 // of the batch's targets.
-Split default_split(const Grid3 &g, double share = 1.0, const Targets &tg = kDefaultTargets);
+Split default_split(const Grid3 &g, double share = 1.0, const Targets &tg = kDefaultTargets,
+                    int R = 9, int halo = 9);
 // Split of a single volume from the resident capacity of the z and update
 // passes (R: Gaussian radius): z chunks are chosen so that the launches' last
 // round of workgroups is not left nearly empty, and down to 2 slices long where
@@ -189,15 +178,21 @@ Split capacity_split(const Grid3 &g, int R, int halo);
 // 8 per CU) and the update pass (512-thread groups at 2 per CU), on 256 CUs.
 constexpr int64_t kResidentZ = 2048;
 constexpr int64_t kResidentU = 512;
-// Workgroups of `waves` waves of the xy pass resident at once: 3 waves per
-// SIMD up to radius 9, 2 above (registers); at most 4 groups per CU, 2 of
-// the large ones (LDS).
-inline int64_t resident_f(int R, int nw, int waves)
+// Waves of the xy pass's march that a SIMD holds (registers): what the kernels
+// are compiled for (`two`: with both Gaussian stages), the most each radius
+// allows without a spill.
+__host__ __device__ constexpr int xyf_simd_waves(int R, bool two)
 {
-    const int by_regs = (R <= 9 ? 12 : 8) / waves, by_lds = nw == 8 ? 2 : 4;
-    const int per_cu = by_regs < by_lds ? by_regs : by_lds;
-    return kCus * (int64_t)(per_cu < 1 ? 1 : per_cu);
+    return two ? (R <= 7 ? 4 : R <= 10 ? 3 : 2) : (R <= 4 ? 5 : R <= 10 ? 4 : R <= 15 ? 3 : 2);
 }
+// Workgroups of `waves` waves that a CU holds: by registers, and by LDS 4 of up
+// to 4 waves or 2 of up to 8, twice that with one stage.
+int xyf_resident(int R, bool two, int nw, int waves);
+// Load of the busiest SIMD while a CU holds `k` such workgroups, in waves: a
+// step of four rows takes a SIMD about 2600 clocks per wave (R = 9; it is bound by
+// the matrix and vector units) and no less than about 3900, one wave's own
+// latency, hence 1.5 or more.
+double xyf_load(int waves, int64_t k);
 // The small-volume form of the xy pass (RSF force): a workgroup of 8 waves
 // holds a chunk's rows in LDS.  Groups of four rows that are x-convolved in
 // stage 1, whose fits are taken, and that are stored, for `len` rows.
@@ -228,23 +223,28 @@ constexpr int64_t kXysLds = 156 * 1024;   // of a CU's 160 KB
 
 // Workgroup size (4 or 8 waves) and row chunks of the xy pass for a single
 // volume, or nw = 2: the small-volume form with f chunks.  For the march: the
-// least time of the busiest CU, in rows.  A step of four rows
-// takes a SIMD about 2600 clocks per resident wave (it is bound by the matrix
-// and vector units) and no less than about 3900 (one wave's own latency), so
-// the time is rounds of resident workgroups x rows (the chunk, `halo` rows of
-// its own and its neighbours' on either side, two groups of latency) x
-// max(1.5, waves per SIMD).  192 x 320 x 352, R = 9, FP16 fields: two strips
-// of 3 waves in two chunks 0.76 x the time of one strip of 6 waves.  The small
-// form's time is that of its products on the busiest CU (each group of four
-// rows of 64 columns 2 (2R + 4) instructions of 8 clocks, 3.6 x that with two
-// waves per SIMD and the rest) plus, per round of resident workgroups, its
-// chain of loads and barriers (about 6 us); 1 us is 3.5 rows in the march's
-// unit.  64^3: 20 -> 12 us; at 108 x 172 x 140, R = 6 it would take 64 us where
-// the march takes 36.
+// least time of the busiest CU, in rows: rounds of resident workgroups x rows
+// (the chunk, R + `halo` rows of its neighbours' on either side, two groups of
+// latency) x load.  192 x 320 x 352, R = 9, FP16 fields: two strips of 3 waves in
+// two chunks 0.76 x the time of one strip of 6 waves.  The small form's time is
+// that of its products on the busiest CU (each group of four rows of 64 columns
+// 2 (2R + 4) instructions of 8 clocks, 3.6 x that with two waves per SIMD and
+// the rest) plus, per round of resident workgroups, its chain of loads and
+// barriers (about 6 us); 1 us is 3.5 rows in the march's unit.  64^3: 20 -> 12
+// us; at 108 x 172 x 140, R = 6 it would take 64 us where the march takes 36.
 struct XyfPick {
     int nw, f;
 };
 XyfPick xyf_pick(const Grid3 &g, int R, int halo);
+// Workgroup size (4 or 8 waves) for a batch of several tiles with row chunks f:
+// the least sum of their workgroups' times.  Two stages recompute a 2R-column
+// halo per strip, so long rows go to 8 waves (512^3, R = 9: one 512-column strip
+// 0.62 ms, three of 183 columns 0.74 ms) unless the strips leave much of such a
+// workgroup's LDS unused and put two waves on one SIMD and one on the others
+// (114- to 274-column tiles: 0.74 ms with 4, 1.33 ms with 8).  Taken over all
+// tiles, not the narrowest: 400 and 600 columns 109 -> 74 us (4 instead of 8),
+// one tile of 100 and six of 512, R = 12, FP16 356 -> 272 (8 instead of 4).
+int xyf_batch_waves(const Grid3 *g, const Split *sp, int n, int R, int halo);
 // Update-pass workgroups of a tile under any valid split are at most this:
 // chunks of 8 slices, or, where those are fewer than the GPU holds, of 2.
 __host__ __device__ inline int64_t u_blocks_max(const Grid3 &g)

@@ -370,7 +370,8 @@ bool launch_chunk(rsf_server *s, std::string &why)
         for (Tile *t : fin) vox_fin += (double)t->g.nx * t->g.ny * t->g.nz;
         auto desc_of = [&](Tile *t, double total) {
             const double share = (double)t->g.nx * t->g.ny * t->g.nz / total;
-            Split sp = rsf::default_split(t->g, share, s->targets);
+            Split sp = rsf::default_split(t->g, share, s->targets, gp->R,
+                                          xyf_halo(gp->req.params.force, gp->R));
             if (fuse) sp.u = 1;
             int *flags = reinterpret_cast<int *>(reinterpret_cast<char *>(s->flags_dev) +
                                                  (size_t)t->slot * kSlotBytes);

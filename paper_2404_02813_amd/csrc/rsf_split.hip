@@ -21,7 +21,8 @@ static int chunks(int64_t n, int64_t cols, int64_t want_blocks, int64_t least)
     return (int)((n + len - 1) / len);
 }
 
-Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_target)
+Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_target, int R,
+                 int halo)
 {
     Split s;
     const int64_t strips = nbx64(g.nx);
@@ -29,7 +30,8 @@ Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_t
     s.z = chunks(g.nz, z_cols(g), z_target, 8);
     s.u = chunks(g.nz, (int64_t)((g.nx + kUx - 1) / kUx) * ((g.ny + kUy - 1) / kUy), u_target, 8);
     // an xy-pass workgroup holds several waves and pays a halo of up to 4 R rows
-    s.f = chunks(g.ny, (int64_t)xyf_strips(g.nx, 9, xyf_waves(g.nx, 9)).n * g.nz, xy_waves / 16, 32);
+    const int nw = xyf_batch_waves(&g, &s, 1, R, halo);
+    s.f = chunks(g.ny, (int64_t)xyf_strips(g.nx, halo, nw).n * g.nz, xy_waves / 16, 32);
     return s;
 }
 
@@ -37,12 +39,12 @@ Split make_split(const Grid3 &g, int64_t xy_waves, int64_t z_target, int64_t u_t
 // the batch's workgroup targets (by default xy ~16K waves, rows in chunks of
 // at most 128; z ~2K workgroups; update ~1K workgroups).  Fewer chunks per tile means fewer
 // halo slices re-read, so small tiles in a big batch run unchunked.
-Split default_split(const Grid3 &g, double share, const Targets &tg)
+Split default_split(const Grid3 &g, double share, const Targets &tg, int R, int halo)
 {
     const auto part = [&](int64_t n) {
         return (int64_t)std::max(1.0, std::ceil((double)n * share));
     };
-    Split s = make_split(g, part(tg.xy), part(tg.z), part(tg.u));
+    Split s = make_split(g, part(tg.xy), part(tg.z), part(tg.u), R, halo);
     const int base = (g.ny + 127) / 128;
     if (s.xy < base) {
         const int64_t len = (g.ny + base - 1) / base;
@@ -115,50 +117,93 @@ static int few_z(int64_t nz, int64_t cols, int64_t most)
     return best;
 }
 
+int xyf_resident(int R, bool two, int nw, int waves)
+{
+    const int by_regs = 4 * xyf_simd_waves(R, two) / waves, by_lds = (nw == 8 ? 2 : 4) * (two ? 1 : 2);
+    return std::max(1, std::min(by_regs, by_lds));
+}
+
+double xyf_load(int waves, int64_t k)
+{
+    // (more than four waves load the busiest SIMD as a multiple of four)
+    const int on_simds = waves > 4 ? (waves + 3) / 4 * 4 : waves;
+    return std::max(1.5, 0.25 * (double)(k * on_simds));
+}
+
+// Rows of a chunk of `len` rows, one of c: its own, `reach` rows above and below
+// where it has neighbours, and two groups of latency.
+static int xyf_rows(int len, int c, int reach)
+{
+    return len + (c == 1 ? 0 : c == 2 ? reach : 2 * reach) + 8;
+}
+
+// f(c, length) for the chunk counts c <= most of n rows that give c non-empty
+// chunks of ceil(n / c): about 2 sqrt(n) of them.
+template <class F>
+static void each_chunking(int n, int most, F &&f)
+{
+    for (int c = 1; c <= most;) {
+        const int len = (n + c - 1) / c;
+        f(c, len);
+        if (len == 1) break;
+        c = (n + len - 2) / (len - 1);
+    }
+}
+
 XyfPick xyf_pick(const Grid3 &g, int R, int halo)
 {
     XyfPick best{4, 1};
     double least = -1.0;
-    const int reach = 2 * (R + halo);   // R (+ R with two stages) above and below
-    for (int nw = 4; nw <= (halo > 0 ? 8 : 4); nw += 4) {
+    const bool two = halo > 0;
+    const int most = (g.ny + 3) / 4;
+    const auto better = [&](double cost, int nw, int c) {
+        if (least >= 0.0 && cost >= 0.97 * least) return;
+        least = cost;
+        best = XyfPick{nw, c};
+    };
+    for (int nw = 4; nw <= (two ? 8 : 4); nw += 4) {
         const XyfStrips st = xyf_strips(g.nx, halo, nw);
         const int waves = (st.width + 63) / 64;
-        const int64_t slots = resident_f(R, nw, waves) / kCus;
-        for (int c = 1; c <= (g.ny + 3) / 4; ++c) {
-            const int len = (g.ny + c - 1) / c;
-            if ((g.ny + len - 1) / len != c) continue;
+        const int64_t slots = xyf_resident(R, two, nw, waves);
+        each_chunking(g.ny, most, [&](int c, int len) {
             const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
             const int64_t at_once = std::min(per_cu, slots);
-            // (more than four waves load the busiest SIMD as a multiple of four)
-            const int on_simds = waves > 4 ? (waves + 3) / 4 * 4 : waves;
-            const double load = std::max(1.5, 0.25 * (double)(at_once * on_simds));
-            const int rows = len + (c == 1 ? 0 : c == 2 ? reach / 2 : reach) + 8;
-            const double cost = (double)((per_cu + at_once - 1) / at_once) * rows * load;
-            if (least < 0.0 || cost < 0.97 * least) {
-                least = cost;
-                best = XyfPick{nw, c};
-            }
-        }
+            better((double)((per_cu + at_once - 1) / at_once) * xyf_rows(len, c, R + halo) *
+                       xyf_load(waves, at_once),
+                   nw, c);
+        });
     }
-    if (halo == 0) return best;
+    if (!two) return best;
     const XyfStrips st = xyf_strips(g.nx, halo, 2);
     const int waves = (st.width + 63) / 64;
-    for (int c = 1; c <= (g.ny + 3) / 4; ++c) {
-        const int len = (g.ny + c - 1) / c;
+    each_chunking(g.ny, most, [&](int c, int len) {
         const int64_t lds = xys_lds(len, R, waves);
-        if ((g.ny + len - 1) / len != c || lds > kXysLds) continue;
+        if (lds > kXysLds) return;
         const XysRows n = xys_rows(len, R);
         const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
         const int64_t at_once = std::min(per_cu, std::min<int64_t>(2, kXysLds / lds));
         const double work =
             (n.a + 2 * n.b + n.c) * waves * 2.0 * (2 * R + 4) * 8.0 / 4.0 * 3.6 / 2300.0;
         const double us = (double)((per_cu + at_once - 1) / at_once) * 6.0 + per_cu * work;
-        if (3.5 * us < 0.97 * least) {
-            least = 3.5 * us;
-            best = XyfPick{2, c};
-        }
-    }
+        better(3.5 * us, 2, c);
+    });
     return best;
+}
+
+int xyf_batch_waves(const Grid3 *g, const Split *sp, int n, int R, int halo)
+{
+    if (halo == 0) return 4;
+    double cost[2] = {0.0, 0.0};
+    for (int k = 0; k < 2; ++k)
+        for (int t = 0; t < n; ++t) {
+            const int nw = 4 + 4 * k;
+            const XyfStrips st = xyf_strips(g[t].nx, halo, nw);
+            const int waves = (st.width + 63) / 64, slots = xyf_resident(R, true, nw, waves);
+            const int len = (g[t].ny + sp[t].f - 1) / sp[t].f;
+            cost[k] += (double)st.n * g[t].nz * sp[t].f * xyf_rows(len, sp[t].f, R + halo) *
+                       xyf_load(waves, slots) / slots;
+        }
+    return cost[1] < cost[0] ? 8 : 4;
 }
 
 Split capacity_split(const Grid3 &g, int R, int halo)

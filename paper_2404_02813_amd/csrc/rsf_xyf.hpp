@@ -141,15 +141,6 @@ __device__ __forceinline__ void bst_at(rsrc_t r, uint32_t off, T v)
     }
 }
 
-// Waves per SIMD the march is compiled for: the most its registers allow with
-// no spill (a bound one higher puts 8 to 24 bytes a lane in scratch).
-template <int R, int MODE, bool PROBE, class ST>
-constexpr int xyf_min_waves =
-    PROBE             ? (R <= 9 ? 3 : 2)
-    : MODE == XY_RSF  ? (R <= 7 ? 4 : R <= 9 ? 3 : 2)
-    : sizeof(ST) == 2 ? (R <= 6 ? 5 : R <= 11 ? 4 : 3)
-                      : (R <= 4 ? 5 : R <= 10 ? 4 : R <= 15 ? 3 : 2);
-
 // A workgroup owns a strip of at most 64 NW columns of one slice (64 per
 // wave) and a chunk of rows, and marches down it four rows per step.  Step G:
 //   - rows of group G (with an R halo in x) are in LDS; each lane x-convolves
@@ -165,7 +156,8 @@ constexpr int xyf_min_waves =
 // loaded meanwhile; one barrier per step.
 template <int R, int MODE, bool PROBE, int NW, class ST, class IMG>
 __global__ __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(xyf_min_waves<R, MODE, PROBE, ST>))) void xyf_kernel(Batch bt, Taps t, Coeffs c)
+__attribute__((amdgpu_waves_per_eu(PROBE ? 2 : xyf_simd_waves(R, MODE == XY_RSF))))
+void xyf_kernel(Batch bt, Taps t, Coeffs c)
 {
     constexpr bool TWO = MODE == XY_RSF;
     constexpr int NG = (2 * R + 3) / 4 + 1;          // open output groups
