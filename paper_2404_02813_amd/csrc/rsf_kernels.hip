@@ -351,7 +351,13 @@ __device__ __forceinline__ float godunov(float &a, float b, float c)
 // The block's lines and one line around them are loaded skewed, [s][k'][j'],
 // kSs + 2 planes (absent points as kFar); thread (j', k') updates its point of
 // one plane after the other, one barrier each, and a block that changed is
-// written back.
+// written back.  The load also takes in points that no update reads, on lines
+// and planes off the block along two axes at once: those of the blocks
+// (b - 1; J + 1, K), (b + 1; J - 1, K), (b; J + 1, K - 1) and the like, which
+// belong to the same launch and may be writing them.  An update reads the
+// points one step along one axis only: planes s - 1 and s + 1 of its own line,
+// s - 1 of the lines j' - 1 and k' - 1, s + 1 of j' + 1 and k' + 1; those lie in
+// blocks of launches before or after this one.
 //
 // What bounds it is the chain of dependent steps: (nx + ny + nz) / kSs +
 // (ny + nz) / kSj launches a sweep, each a block's load, kSs steps and its
@@ -576,13 +582,12 @@ int64_t sweep_wavefronts(int64_t nx, int64_t ny, int64_t nz)
 hipError_t launch_sweep_blocks(float *u, int64_t nx, int64_t ny, int64_t nz, int dir, int64_t W,
                                hipStream_t s)
 {
-    // (hyperplane numbers and block indices are 32 bits wide; every dimension
-    // is at most 2^28, so their sums fit)
+    // (hyperplane numbers and block indices are 32 bits wide: nx ny <= 2^28 and
+    // nz <= 2^30, so nx + ny + nz fits)
     const int64_t nbj = (ny + kSj - 1) / kSj, nbk = (nz + kSj - 1) / kSj,
                   nb = (nx + ny + nz - 2 + kSs - 1) / kSs;
-    // block diagonals D = J + K with b = W - D hyperplanes in the volume: the
-    // block's first is s = kSs b, its lines span kSj D .. kSj D + 2 (kSj - 1)
-    // + nx - 1
+    // block diagonals D = J + K for which b = W - D is one of the nb blocks of
+    // hyperplanes; those whose lines have no point on them leave in the kernel
     const int64_t dlo = std::max<int64_t>(0, W - (nb - 1));
     const int64_t dhi = std::min<int64_t>(nbj + nbk - 2, W);
     if (dhi < dlo) return hipSuccess;
