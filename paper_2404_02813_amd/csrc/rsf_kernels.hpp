@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         constexpr bool kVTaps =
             !PROBE && (FUSE ? (PACK ? R <= 10 : R <= 7)
                             : !PAPER && !(R == 10 && std::is_same<ST, float>::value &&
-                                std::is_same<IT, uint16_t>::value));
+                                          std::is_same<IT, uint16_t>::value));
         float tv[kVTaps ? R + 1 : 1];
         if constexpr (kVTaps) {
 #pragma unroll
@@ -791,8 +791,8 @@ __global__ __launch_bounds__(kUThreads, 4) void z_update_kernel(Batch bt, Taps t
         }
         // The fused RSF update marches its blocks near the far end without the
         // branches too: a volume of few slices has no other.  16 x 512 x 512,
-        // FP16, R = 5: 38.9 us with only the fast blocks, 35.8 with both
-        // (40 slices, R = 9: 81.6 and 77.4).
+        // FP16, R = 5: 38.9 us with only the fast blocks, 35.8 with both; 40
+        // slices, R = 9: 81.6 and 77.4.
         if constexpr (FUSE && !PAPER) {
             static_assert(PF == 1, "the fused RSF update runs one prefetch stage");
             for (; zb + M <= zt.z1; zb += M) {
