@@ -186,7 +186,11 @@ __host__ __device__ constexpr int xyf_simd_waves(int R, bool two)
     return two ? (R <= 7 ? 4 : R <= 10 ? 3 : 2) : (R <= 4 ? 5 : R <= 10 ? 4 : R <= 15 ? 3 : 2);
 }
 // Workgroups of `waves` waves that a CU holds: by registers, and by LDS 4 of up
-// to 4 waves or 2 of up to 8, twice that with one stage.
+// to 4 waves or 2 of up to 8.  One stage is planned with 3 waves per SIMD up to
+// R = 9, 2 above and 4 workgroups, which is fewer than fit: its large volumes are
+// bound by HBM, and a plan that fills every place once, so that all chunks march
+// in step, is the slower one (512^3, R = 9: one chunk in one round of 4 per CU
+// 606 us, three chunks 567).
 int xyf_resident(int R, bool two, int nw, int waves);
 // Load of the busiest SIMD while a CU holds `k` such workgroups, in waves: a
 // step of four rows takes a SIMD about 2600 clocks per wave (R = 9; it is bound by

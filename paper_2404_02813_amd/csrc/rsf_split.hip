@@ -119,8 +119,8 @@ static int few_z(int64_t nz, int64_t cols, int64_t most)
 
 int xyf_resident(int R, bool two, int nw, int waves)
 {
-    const int by_regs = 4 * xyf_simd_waves(R, two) / waves, by_lds = (nw == 8 ? 2 : 4) * (two ? 1 : 2);
-    return std::max(1, std::min(by_regs, by_lds));
+    const int simd = two ? xyf_simd_waves(R, true) : (R <= 9 ? 3 : 2);
+    return std::max(1, std::min(4 * simd / waves, nw == 8 ? 2 : 4));
 }
 
 double xyf_load(int waves, int64_t k)
