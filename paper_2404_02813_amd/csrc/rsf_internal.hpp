@@ -233,9 +233,11 @@ constexpr int64_t kXysLds = 156 * 1024;   // of a CU's 160 KB
 // two chunks 0.76 x the time of one strip of 6 waves.  The small form's time is
 // that of its products on the busiest CU (each group of four rows of 64 columns
 // 2 (2R + 4) instructions of 8 clocks, 3.6 x that with two waves per SIMD and
-// the rest) plus, per round of resident workgroups, its chain of loads and
-// barriers (about 6 us); 1 us is 3.5 rows in the march's unit.  64^3: 20 -> 12
-// us; at 108 x 172 x 140, R = 6 it would take 64 us where the march takes 36.
+// the rest) plus its chain of loads and barriers (about 6 us); 1 us is 3.5 rows
+// in the march's unit.  64^3: 20 -> 12 us; at 108 x 172 x 140, R = 6 it would take
+// 64 us where the march takes 36.  It is taken in one round of workgroups only: a
+// second one has nothing to overlap its chain with (169 x 304 x 56, R = 5: 39 us
+// in two rounds, the march 27).
 struct XyfPick {
     int nw, f;
 };

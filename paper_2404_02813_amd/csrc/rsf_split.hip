@@ -181,11 +181,10 @@ XyfPick xyf_pick(const Grid3 &g, int R, int halo)
         if (lds > kXysLds) return;
         const XysRows n = xys_rows(len, R);
         const int64_t per_cu = ((int64_t)st.n * g.nz * c + kCus - 1) / kCus;
-        const int64_t at_once = std::min(per_cu, std::min<int64_t>(2, kXysLds / lds));
+        if (per_cu > std::min<int64_t>(2, kXysLds / lds)) return;   // one round
         const double work =
             (n.a + 2 * n.b + n.c) * waves * 2.0 * (2 * R + 4) * 8.0 / 4.0 * 3.6 / 2300.0;
-        const double us = (double)((per_cu + at_once - 1) / at_once) * 6.0 + per_cu * work;
-        better(3.5 * us, 2, c);
+        better(3.5 * (6.0 + per_cu * work), 2, c);
     });
     return best;
 }

@@ -98,6 +98,9 @@ static int run()
         CHECK(f.nw == 4 || (force == RSF_FORCE_RSF && (f.nw == 2 || f.nw == 8)));
         CHECK(f.nw == 2 ? f.lds > 0 && f.lds <= kXysLds && f.threads == kXysThreads
                         : f.threads <= 64 * f.nw && f.threads >= std::min(xyf_strips(q.nx, halo, f.nw).width, 64));
+        // the small form's workgroups run in one round
+        if (f.nw == 2)
+            CHECK(xyf_blocks(q, s, halo, 2) <= kCus * std::min<int64_t>(2, kXysLds / f.lds));
         if (launch({q}, {s}, R, halo, f.nw)) return 1;
         // a batch
         std::vector<Grid3> g;
