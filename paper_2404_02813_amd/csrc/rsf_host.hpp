@@ -270,6 +270,17 @@ inline int64_t balance_xcds(Batch &b, PassKind k, const std::vector<Grid3> &g,
         }
     }
     while (cut <= kXcds) b.xcd[cut++] = (int)nblocks;
+    // A single volume whose workgroups all run at once takes the time of the CU
+    // that holds most of them: no range longer than its XCD's share of the fewest
+    // workgroups per CU (17 x 102 x 249, R = 7: the small form's 255 workgroups of
+    // the xy pass with 33 on one XCD's 32 CUs 27.7 us, without 16.9).
+    if (k != PASS_XY && g.size() == 1 && nblocks <= 4 * kCus) {
+        const int64_t cap = (nblocks + kCus - 1) / kCus * (kCus / kXcds);
+        for (int x = 1; x < kXcds; ++x) {
+            const int64_t lo = std::max<int64_t>(b.xcd[x - 1], nblocks - cap * (kXcds - x));
+            b.xcd[x] = (int)std::min(std::max<int64_t>(b.xcd[x], lo), b.xcd[x - 1] + cap);
+        }
+    }
     int64_t longest = 0;
     for (int x = 0; x < kXcds; ++x) longest = std::max<int64_t>(longest, b.xcd[x + 1] - b.xcd[x]);
     return longest * kXcds;

@@ -75,7 +75,11 @@ static int launch(const std::vector<Grid3> &g, const std::vector<Split> &sp, int
         most = std::max(most, c);
         sum += c;
     }
-    CHECK(most <= sum / kXcds + one + 1e-9);
+    // balanced in cost, or, where all workgroups of a volume run at once, in number
+    if (g.size() == 1 && start.back() <= 4 * kCus)
+        CHECK(longest <= (start.back() + kCus - 1) / kCus * (kCus / kXcds));
+    else
+        CHECK(most <= sum / kXcds + one + 1e-9);
     return 0;
 }
 
