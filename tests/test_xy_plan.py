@@ -44,3 +44,12 @@ def test_form_of_a_volume(check, radius, shape, waves, chunks):
 @pytest.mark.parametrize("radius,shapes,waves", BATCHES)
 def test_form_of_a_batch(check, radius, shapes, waves):
     assert check(radius, 0, *sum(shapes, ())).split()[0] == str(waves)
+
+
+# strips times slices fill the CUs: a third chunk evens the SIMDs' loads, one of
+# 128^3 or less is cut by their mean
+@pytest.mark.parametrize("force,radius,shape,chunks", [
+    (0, 6, (257, 301, 316), 3), (0, 6, (300, 300, 100), 3), (1, 9, (628, 601, 88), 3),
+    (0, 3, (192, 320, 352), 2), (1, 3, (192, 320, 352), 2), (0, 6, (128, 128, 128), 6)])
+def test_row_chunks(check, force, radius, shape, chunks):
+    assert check(radius, force, *shape).split() == ["4", str(chunks)]
